@@ -6,24 +6,36 @@
 // layer's projections (apb_layer.hip) and the first layer of the retaining
 // head (apb_scorer.hip).  One kernel template covers them: bf16 MFMA
 // 16x16x32 with fp32 accumulation, output features on the MFMA M side (the
-// weights are the A operand) and tokens on the N side, a 256 x 256
-// workgroup tile of 4 waves (2 x 2, each 128 features x 128 tokens in 64
-// 16 x 16 blocks, one wave per SIMD, accumulators in AGPRs), K steps of 64
-// whose weight and token slabs are copied HBM -> LDS by
-// global_load_lds_dwordx4 into XOR-swizzled tiles in two stages.  (16x16x32
+// weights are the A operand) and tokens on the N side, a workgroup tile of
+// 256 features x 32 * NB tokens computed by 4 waves (2 x 2, each 128 features
+// x 16 * NB tokens), K steps of 64 whose weight and token slabs are copied
+// HBM -> LDS by global_load_lds_dwordx4 into XOR-swizzled tiles.  (16x16x32
 // rather than 32x32x16: the same LDS bytes per flop and half the
 // accumulator traffic, which this power-limited chip turns into clock.)
 // Neither a copy nor an operand read spends a vector instruction on its
 // address: a copy is a scalar base plus a fixed per-lane offset, a read one
-// XOR of a per-lane base plus an instruction offset.  The step boundary is
-// software-pipelined: at its last 32-deep substep a wave waits
-// for its copies of the next step, passes the barrier, and issues that
-// substep's MFMAs with the next step's first operand reads and the copies of
-// the step after it (into the stage just finished) spread among them (for
-// long K loops the copies start earlier, behind a second barrier that marks
-// the stage free); the last two steps are peeled so the steady-state loop
-// has no branches (the compiler can then count outstanding LDS reads
-// exactly).
+// XOR of a per-lane base plus an instruction offset.
+//  * NB = 8 (256 tokens), for products that fill the chip with such tiles:
+//    one wave per SIMD, 256 accumulator registers, two LDS stages.  The step
+//    boundary is software-pipelined: at its last 32-deep substep a wave waits
+//    for its copies of the next step, passes the barrier, and issues that
+//    substep's MFMAs with the next step's first operand reads and the copies
+//    of the step after it (into the stage just finished) spread among them
+//    (for long K loops the copies start earlier, behind a second barrier that
+//    marks the stage free); the last two steps are peeled so the steady-state
+//    loop has no branches (the compiler can then count outstanding LDS reads
+//    exactly).
+//  * NB = 2, 3, 4 (64, 96, 128 tokens), for products that would leave CUs
+//    idle: bound by the copies, which a CU takes at 31 cycles per KiB (about
+//    70 GB/s) whatever their pattern, 40 to 48 of them per step beside 512 to
+//    1024 cycles of MFMAs.  Four further waves issue them (two waves per SIMD,
+//    three LDS stages), so that no MFMA queues behind a copy: 1000 tokens x
+//    1024 features at K = 6144 in 128-token tiles took 88 us with the copies
+//    in the computing waves, 63 us with waves of their own (256-token tiles:
+//    122 us).  Deeper rings, other read spacings and prefetches into L2 gave
+//    nothing (the CU's copy rate is the limit, not latency).  The whole layer
+//    at 1256 tokens: 1079 -> 666 us; the retaining head of 8192 tokens:
+//    151 -> 88 us.
 // The token operand is read row-major [t][k], head-major [k / dh][t][dh]
 // (the attention output, whose heads are the O projection's K dimension), or
 // from the head-major Q, K and V tensors as one [Q heads; K heads; V heads]
@@ -42,6 +54,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "apb_internal.h"
@@ -56,11 +69,10 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 
 constexpr int kBF = 256;        // weight rows (output features) per workgroup
-constexpr int kBT = 256;        // tokens per workgroup
 constexpr int kBK = 64;         // K per step
 constexpr int kGemmThreads = 256;
-constexpr int kPieces = 8;      // 1 KiB copy pieces per slab per wave per step
-constexpr int kTileElems = kBF * kBK;  // = kBT * kBK
+constexpr int kPieces = 8;      // 1 KiB weight copy pieces per wave per step
+constexpr int kGemmCus = 256;   // workgroups of one round (one per CU)
 
 enum XMode { kXRowMajor = 0, kXHeadMajor = 1, kXQkv = 2 };
 enum WMode { kWPlain = 0, kWGateUp = 1 };
@@ -88,8 +100,8 @@ struct GemmParams {
   const float* b1;        // [F]
   const float* w2;        // [n_kv][F]
   float* part;            // [F / kBF][n_kv][T] fp32 partial scores per feature block
-  // tile grid (set by launch_gemm): token tiles, feature tiles, 8-tile blocks along tokens
-  int ntx, nfy, nbt;
+  // tile grid (set by launch_gemm): token tiles from token t_begin on, feature tiles
+  int ntx, nfy, t_begin;
 };
 
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
@@ -101,60 +113,91 @@ __device__ __forceinline__ uint32_t lds_offset(const void* p) {
 // land on 16 distinct 16-byte slots of the 256 bank bytes.
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
-// EARLY: the two-barrier step (long K loops), else one barrier per step.
-template <int XM, int WM, int EPI, bool EARLY>
-__global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
+// NB: 16-token blocks per wave, i.e. a tile of 256 features x 32 * NB tokens.
+// EARLY: the two-barrier step (long K loops, NB = 8), else one barrier per step.
+template <int XM, int WM, int EPI, int NB, bool EARLY>
+__global__ void __launch_bounds__(NB < 8 ? 2 * kGemmThreads : kGemmThreads, 1)
+gemm_kernel(GemmParams p) {
+  constexpr int BT = 32 * NB;                 // tokens per workgroup
+  constexpr int NST = NB == 8 ? 2 : 3;        // LDS stages
+  constexpr int CPS = kPieces + NB;           // copies per wave per step
+  // NB < 8: waves 4..7 do the copies and waves 0..3 the rest (below)
+  constexpr bool SPLIT = NB < 8;
+  constexpr int NMF = 8 * NB;                 // MFMAs per 32-deep substep
+  constexpr int NRD = 8 + NB;                 // operand reads per substep
+  static_assert(!EARLY || NB == 8, "the two-barrier step is scheduled for 64 MFMAs");
   // 256-byte aligned: operand addresses XOR step bits into the low byte of
   // a stage base plus lane offset
-  __shared__ __attribute__((aligned(256))) uint16_t a_lds[2][kTileElems];  // weight slab
-  __shared__ __attribute__((aligned(256))) uint16_t b_lds[2][kTileElems];  // token slab
+  __shared__ __attribute__((aligned(256))) uint16_t a_lds[NST][kBF * kBK];  // weight slabs
+  __shared__ __attribute__((aligned(256))) uint16_t b_lds[NST][BT * kBK];   // token slabs
+
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = wave_id & 3;             // wave among the copying or the computing four
   const int wm = wave & 1, wn = wave >> 1;  // feature half, token half
-  // Blocked, XCD-aware tile order: workgroup b runs on XCD b % 8, and the 32
-  // consecutive workgroups of one XCD take one block of 4 feature x 8 token
-  // tiles, starting and finishing together, so per K step the XCD's L2
-  // fetches 4 weight and 8 token slabs for 32 workgroups (with the tiles
-  // dealt in grid order the same L2 fetched 1.2-3x the bytes).
-  const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
-  const int blk = (slot >> 5) * 8 + xcd, sb = slot & 31;
-  const int ftile = (blk / p.nbt) * 4 + (sb >> 3), ttile = (blk % p.nbt) * 8 + (sb & 7);
-  if (ftile >= p.nfy || ttile >= p.ntx) return;  // past the grid's edge
-  const int t0 = ttile * kBT;
+  // XCD-aware tile order: workgroup b runs on XCD b % 8, and each XCD takes
+  // one contiguous eighth (to within one tile) of the tiles, ordered in
+  // columns of 4 feature tiles: the 32 tiles an XCD works on at a time are 4
+  // feature x 8 token tiles, so per K step its L2 fetches 4 weight and 8
+  // token slabs for 32 workgroups, and no XCD gets a round more than another.
+  const int ntiles = p.ntx * p.nfy;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int per = ntiles >> 3, rem = ntiles & 7;
+  if (slot >= per + (xcd < rem ? 1 : 0)) return;
+  const int tile = xcd * per + min(xcd, rem) + slot;
+  const int col = tile / (4 * p.ntx), in_col = tile - col * 4 * p.ntx;
+  const int width = min(4, p.nfy - 4 * col);
+  const int ttile = in_col / width, ftile = 4 * col + (in_col - ttile * width);
+  const int t0 = p.t_begin + ttile * BT;
   const int f0 = ftile * (WM == kWGateUp ? kBF / 2 : kBF);
   const int nk = p.K / kBK;
+  // With at most 4 feature tiles (the retaining head) every XCD reads the same
+  // weights: each starts its K loop an eighth further on, so that they do not
+  // all fetch one K slab from HBM at a time (weights not in cache, 1000 tokens
+  // x 1024 units: 77 -> 58 us; more feature tiles: no gain).
+  const int k_first = SPLIT && p.nfy <= 4 ? xcd * nk / 8 : 0;
 
   // ---- copies: piece j (8 rows x 128 bytes) of each slab; wave w copies
-  // pieces 8w .. 8w+7.  Lane l takes row l/8 of the piece and fetches the
-  // chunk that belongs at slot l%8.  Rows past the last feature or token
-  // repeat it (their results are never stored).  A copy is a scalar base (the
-  // operand's first row for this workgroup, advanced by the K step in scalar
-  // registers) plus a fixed per-lane byte offset: no vector instruction.
+  // weight pieces 8w .. 8w+7 and token pieces NB*w .. NB*w + NB-1.  Lane l
+  // takes row l/8 of the piece and fetches the chunk that belongs at slot
+  // l%8.  Rows past the last feature or token repeat it (their results are
+  // never stored).  A copy is a scalar base (the operand's first row for this
+  // workgroup, advanced by the K step in scalar registers) plus a fixed
+  // per-lane byte offset: no vector instruction.
   const int cp_row = lane >> 3, cp_slot = lane & 7;
   const int x_ld = XM == kXRowMajor ? p.K : p.dh;  // elements between token rows
   // head-major operands: head dims are a power of two (64 or 128)
   const int dh_shift = XM == kXRowMajor ? 0 : 31 - __builtin_clz((unsigned)p.dh);
-  uint32_t w_off[kPieces], x_off[kPieces];
+  // (set_offsets is called by the copying waves alone: live in the others,
+  // the offsets would spill)
+  uint32_t w_off[kPieces], x_off[NB];
+  auto set_offsets = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < kPieces; ++i) {
-    const int rho = 8 * (kPieces * wave + i) + cp_row;  // slab row 0..255
-    const int chunk = 8 * (cp_slot ^ swz(rho));
-    int fr = WM == kWGateUp ? f0 + 64 * (rho >> 7) + (rho & 63) : f0 + rho;
-    fr = min(fr, p.F - 1);
-    w_off[i] = 2u * (uint32_t)((fr - f0) * p.K + chunk);
-    const int tr = min(t0 + rho, p.T - 1);
-    x_off[i] = 2u * (uint32_t)((tr - t0) * x_ld + chunk);
-  }
+    for (int i = 0; i < kPieces; ++i) {
+      const int rho = 8 * (kPieces * wave + i) + cp_row;  // weight slab row 0..255
+      const int chunk = 8 * (cp_slot ^ swz(rho));
+      int fr = WM == kWGateUp ? f0 + 64 * (rho >> 7) + (rho & 63) : f0 + rho;
+      fr = min(fr, p.F - 1);
+      w_off[i] = 2u * (uint32_t)((fr - f0) * p.K + chunk);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int rho = 8 * (NB * wave + i) + cp_row;  // token slab row 0..BT-1
+      const int chunk = 8 * (cp_slot ^ swz(rho));
+      const int tr = min(t0 + rho, p.T - 1);
+      x_off[i] = 2u * (uint32_t)((tr - t0) * x_ld + chunk);
+    }
+  };
   const uint16_t* const w_first = p.w + (size_t)f0 * p.K;
   const uint16_t* const w_up_first = (WM == kWGateUp ? p.w_up : p.w) + (size_t)f0 * p.K;
   const uint16_t* const x_first = p.x + (size_t)t0 * x_ld;
-  // copy q (0..15) of step kk into stage st: q < 8 weight pieces, else token pieces
+  // copy q (0..CPS-1) of step kk into stage st: q < 8 weight pieces, else token pieces
   auto copy = [&](int kk, int st, int q) __attribute__((always_inline)) {
-    const int k0 = kk * kBK;
-    const int i = q & 7;
-    const int j = kPieces * wave + i;
-    if (q < 8) {
+    const int kr = kk + k_first < nk ? kk + k_first : kk + k_first - nk;
+    const int k0 = kr * kBK;
+    if (q < kPieces) {
+      const int i = q, j = kPieces * wave + i;
       // gate/up: rows 64..127 of either 128-row half are up-projection rows
       const uint16_t* base =
           (WM == kWGateUp && ((kPieces * wave + i) & 15) >= 8 ? w_up_first : w_first) + k0;
@@ -163,6 +206,7 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
                    "s"(d)
                    : "memory");
     } else {
+      const int i = q - kPieces, j = NB * wave + i;
       const uint16_t* base;
       if constexpr (XM == kXRowMajor) {
         base = x_first + k0;
@@ -186,6 +230,46 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
     }
   };
 
+  // prologue: the first NST steps' copies issued, step 0's landed
+  auto first_copies = [&]() __attribute__((always_inline)) {
+    set_offsets();
+#pragma unroll
+    for (int k0 = 0; k0 < NST; ++k0) {
+      if (k0 < nk) {
+#pragma unroll
+        for (int q = 0; q < CPS; ++q) copy(k0, k0, q);
+      }
+    }
+    if (nk >= NST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * CPS) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_barrier" ::: "memory");
+  };
+  // The copying waves.  A CU takes one 1 KiB copy per 31 cycles whatever the
+  // access pattern, so below 256 tokens a step's copies outlast its MFMAs, and
+  // a wave that does both stalls its MFMAs behind the copies it issues.  One
+  // barrier per step, shared with the computing waves' barrier B: before it
+  // step kk+1 has landed, after it stage kk % NST is free for step kk+NST.
+  if constexpr (SPLIT) {
+    if (wave_id >= 4) {
+      first_copies();
+      int st = 0;
+      for (int kk = 0; kk + 1 < nk; ++kk) {
+        if (kk + NST <= nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * CPS) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("s_barrier" ::: "memory");
+        if (kk + NST < nk) {
+#pragma unroll
+          for (int q = 0; q < CPS; ++q) copy(kk + NST, st, q);
+        }
+        st = st + 1 == NST ? 0 : st + 1;
+      }
+      return;
+    }
+  } else {
+    first_copies();
+  }
+  if constexpr (SPLIT) asm volatile("s_barrier" ::: "memory");
+
   // ---- operands (16x16x32 MFMAs): lane (li, lg) of a 16-row block reads
   // slab row 16*blk + li, K elements 32*kc + 8*lg .. +7, i.e. chunk
   // 4*kc + lg of that row, stored at slot (4*kc + lg) ^ swz(row).
@@ -196,96 +280,100 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
   const int sw = (li >> 1) & 7;
   const uint32_t lane_chunk = (uint32_t)(16 * (lg ^ sw));
   const uint32_t a_lane = (uint32_t)((128 * wm + li) * 128) + lane_chunk;
-  const uint32_t b_lane = (uint32_t)((128 * wn + li) * 128) + lane_chunk;
-  // stage st's row bases (the stages are 32 KiB apart, so the XOR with 64*kc
-  // below touches only the chunk bits)
+  const uint32_t b_lane = (uint32_t)((16 * NB * wn + li) * 128) + lane_chunk;
+  // stage st's row bases (rows are 128 bytes and the slabs 256-byte aligned, so
+  // the XOR with 64*kc below touches only the chunk bits)
   auto a_base = [&](int st) __attribute__((always_inline)) { return lds_offset(a_lds[st]) + a_lane; };
   auto b_base = [&](int st) __attribute__((always_inline)) { return lds_offset(b_lds[st]) + b_lane; };
+  // Operand read of the next substep issued behind MFMA i of a substep (0..7
+  // weight block, 8.. token block), or -1.  SPLIT waves have 256 registers
+  // each, so only the weight blocks 4..7 are double buffered: blocks 0..3 are
+  // read into the registers that the substep's first half has used.
+  auto read_of = [](int i) __attribute__((always_inline)) -> int {
+    if (!SPLIT) return i < 2 * NRD && (i & 1) ? i >> 1 : -1;
+    if (i < 4) return 4 + i;
+    if (i < 4 + NB) return 8 + i - 4;
+    return i >= 4 * NB && i < 4 * NB + 4 ? i - 4 * NB : -1;
+  };
+  auto a_buf = [](int sub, int mb) __attribute__((always_inline)) -> int {
+    return SPLIT && mb < 4 ? 0 : sub;
+  };
   auto read = [](uint32_t base, int blk, int kc) __attribute__((always_inline)) -> bf16x8 {
     return *(const lds_bf16x8*)(uintptr_t)((base ^ (64u * (uint32_t)kc)) + 2048u * (uint32_t)blk);
   };
 
   // acc[mb][nb]: 16 features x 16 tokens; lane (li, lg) holds features
   // 4*lg .. 4*lg+3 of token li
-  f32x4 acc[8][8];
+  f32x4 acc[8][NB];
 #pragma unroll
   for (int mb = 0; mb < 8; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < 8; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[mb][nb][r] = 0.f;
-  bf16x8 av[2][8], bv[2][8];
+  bf16x8 av[2][8], bv[2][NB];
 
-  // prologue: step 0 copied and visible, step 1's copies in flight, step 0's
-  // first operands read
-#pragma unroll
-  for (int q = 0; q < 16; ++q) copy(0, 0, q);
-  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-  if (nk > 1) {
-#pragma unroll
-    for (int q = 0; q < 16; ++q) copy(1, 1, q);
-  }
+  // step 0 is visible: its first operands
 #pragma unroll
   for (int mb = 0; mb < 8; ++mb) av[0][mb] = read(a_base(0), mb, 0);
 #pragma unroll
-  for (int nb = 0; nb < 8; ++nb) bv[0][nb] = read(b_base(0), nb, 0);
+  for (int nb = 0; nb < NB; ++nb) bv[0][nb] = read(b_base(0), nb, 0);
 
-  // One K step in two substeps of 64 MFMAs; the odd MFMAs among the first 32
-  // of a substep each carry one of the next substep's 16 operand reads.
-  // NEXT: step kk+1 exists (at the last substep: wait for its copies,
-  // barrier B, read its first operands); COPY: step kk+2 exists.  Its 16
-  // copies go into the stage this step reads, each on its own MFMA four
-  // apart (issued back to back they stall the wave, and the matrix core with
-  // it, for hundreds of cycles).  That stage is free once every wave has read
-  // the last substep's operands from it.  EARLY marks that point with barrier
-  // A, at MFMA 48 of the first substep, and starts the copies there (4 in
-  // the first substep, 12 in the second), giving them a quarter step more to
-  // land: worth 5% on K loops of hundreds of steps, 1-2% slower on short
-  // ones.  Otherwise the copies start after barrier B, on every fourth MFMA
-  // of the second substep.
-  auto step = [&](int kk, auto next_t, auto copy_t) __attribute__((always_inline)) {
-    constexpr bool NEXT = decltype(next_t)::value, COPY = decltype(copy_t)::value;
-    const int st = kk & 1;
-    const uint32_t ab = a_base(st), bb = b_base(st), ab1 = a_base(st ^ 1), bb1 = b_base(st ^ 1);
+  // One K step in two substeps of NMF MFMAs; MFMAs early in a substep each
+  // carry one of the next substep's NRD operand reads (with 64 MFMAs every
+  // odd one of the first 32).  NEXT: step kk+1 exists (at the last substep:
+  // its copies have landed, barrier B, read its first operands); COPY: step
+  // kk+NST exists and this wave copies.  Its copies go into the stage this
+  // step reads, spread over the substep's MFMAs (issued back to back they
+  // stall the wave, and the matrix core with it, for hundreds of cycles).
+  // That stage is free once every wave has read the last substep's operands
+  // from it.  EARLY marks that point with barrier A, at MFMA 48 of the first
+  // substep, and starts the copies there (4 in the first substep, 12 in the
+  // second), giving them a quarter step more to land: worth 5% on K loops of
+  // hundreds of steps, 1-2% slower on short ones.  Otherwise the copies start
+  // after barrier B.
+  auto step = [&](int kk, int st, auto next_t, auto copy_t) __attribute__((always_inline)) {
+    constexpr bool NEXT = decltype(next_t)::value, COPY = decltype(copy_t)::value && !SPLIT;
+    const int st1 = st + 1 == NST ? 0 : st + 1;
+    const uint32_t ab = a_base(st), bb = b_base(st), ab1 = a_base(st1), bb1 = b_base(st1);
 #pragma unroll
     for (int kc = 0; kc < 2; ++kc) {
       const int cur = kc, nxt = kc ^ 1;
       const bool boundary = kc == 1;
       if (boundary && NEXT) {
-        // barrier B: this wave's copies of step kk+1 have landed (only the
-        // four copies of step kk+2 issued since barrier A may be
-        // outstanding; copies complete in order); after the barrier every
-        // wave's have
-        if constexpr (EARLY && COPY) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+        // barrier B: this wave's copies of step kk+1 have landed; after the
+        // barrier every wave's have
+        if constexpr (SPLIT) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else if constexpr (EARLY && COPY) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
         else if constexpr (EARLY) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       }
 #pragma unroll
-      for (int i = 0; i < 64; ++i) {
-        const int mb = i >> 3, nb = i & 7;
+      for (int i = 0; i < NMF; ++i) {
+        const int mb = i / NB, nb = i % NB;
         if (EARLY && !boundary && COPY && i == 48) {
           // barrier A: every wave's reads of stage st are done
           asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         }
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[cur][mb], bv[cur][nb],
-                                                              acc[mb][nb], 0, 0, 0);
-        if (i < 32 && (i & 1) == 1) {
-          const int j = i >> 1;
+        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            av[a_buf(cur, mb)][mb], bv[cur][nb], acc[mb][nb], 0, 0, 0);
+        const int j = read_of(i);
+        if (j >= 0) {
           if (!boundary) {
-            if (j < 8) av[nxt][j] = read(ab, j, 1);
+            if (j < 8) av[a_buf(nxt, j)][j] = read(ab, j, 1);
             else bv[nxt][j - 8] = read(bb, j - 8, 1);
           } else if (NEXT) {
-            if (j < 8) av[nxt][j] = read(ab1, j, 0);
+            if (j < 8) av[a_buf(nxt, j)][j] = read(ab1, j, 0);
             else bv[nxt][j - 8] = read(bb1, j - 8, 0);
           }
         }
-        if (COPY && (i & 3) == 0) {
-          if constexpr (EARLY) {
+        if constexpr (COPY && EARLY) {
+          if ((i & 3) == 0) {
             if (!boundary && i >= 48) copy(kk + 2, st, (i - 48) >> 2);
             else if (boundary && i < 48) copy(kk + 2, st, 4 + (i >> 2));
-          } else if (boundary) {
-            copy(kk + 2, st, i >> 2);
           }
+        } else if constexpr (COPY) {
+          if (boundary && (i & 3) == 0) copy(kk + 2, st, i >> 2);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -293,13 +381,20 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
   };
   const std::true_type yes{};
   const std::false_type no{};
-  int kk = 0;
-  for (; kk + 2 < nk; ++kk) step(kk, yes, yes);
-  if (kk + 1 < nk) step(kk++, yes, no);
-  step(kk, no, no);
+  int kk = 0, st = 0;
+  auto advance = [&]() __attribute__((always_inline)) {
+    ++kk;
+    st = st + 1 == NST ? 0 : st + 1;
+  };
+  for (; kk + (SPLIT ? 1 : NST) < nk; advance()) step(kk, st, yes, yes);
+  if (kk + 1 < nk) {
+    step(kk, st, yes, no);
+    advance();
+  }
+  step(kk, st, no, no);
 
   // ---- epilogue.  Lane (li, lg), block (mb, nb), element r holds slab row
-  // 128*wm + 16*mb + 4*lg + r of token t0 + 128*wn + 16*nb + li: four
+  // 128*wm + 16*mb + 4*lg + r of token t0 + 16*NB*wn + 16*nb + li: four
   // consecutive features (one 8-byte store).
   if constexpr (EPI == kEpiScorer) {
     // bias, SiLU and this workgroup's share of the second layer: for each of
@@ -308,16 +403,16 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
     __syncthreads();  // every wave is done with the LDS stages
     float* const w2_lds = reinterpret_cast<float*>(&a_lds[0][0]);  // [kBF][kScorerMaxKv]
     float* const b1_lds = w2_lds + kBF * kScorerMaxKv;              // [kBF]
-    float* const red = reinterpret_cast<float*>(&b_lds[0][0]);     // [2][kScorerMaxKv][kBT]
+    float* const red = reinterpret_cast<float*>(&b_lds[0][0]);     // [2][kScorerMaxKv][BT]
     for (int i = tid; i < kBF * kScorerMaxKv; i += kGemmThreads) {
       const int u = i / kScorerMaxKv, kv = i % kScorerMaxKv;
       w2_lds[i] = kv < p.n_kv ? p.w2[(size_t)kv * p.F + f0 + u] : 0.f;
     }
     for (int i = tid; i < kBF; i += kGemmThreads) b1_lds[i] = p.b1[f0 + i];
     __syncthreads();
-    float part[8][kScorerMaxKv];
+    float part[NB][kScorerMaxKv];
 #pragma unroll
-    for (int nb = 0; nb < 8; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int kv = 0; kv < kScorerMaxKv; ++kv) part[nb][kv] = 0.f;
 #pragma unroll
@@ -329,7 +424,7 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
         const f32x4 wb = *reinterpret_cast<const f32x4*>(&w2_lds[u * kScorerMaxKv + 4]);
         const float bias = b1_lds[u];
 #pragma unroll
-        for (int nb = 0; nb < 8; ++nb) {
+        for (int nb = 0; nb < NB; ++nb) {
           // SiLU with the hardware reciprocal (within 1 ulp) instead of an
           // IEEE division, about ten instructions per element
           const float z = acc[mb][nb][r] + bias;
@@ -343,7 +438,7 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
       }
     // the four lane groups hold the same tokens' other features
 #pragma unroll
-    for (int nb = 0; nb < 8; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int kv = 0; kv < kScorerMaxKv; ++kv) {
         float x = part[nb][kv];
@@ -353,24 +448,24 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
     // the two feature halves (wm = 0, 1) of each token half meet in LDS
     if (lg == 0) {
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb)
+      for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int kv = 0; kv < kScorerMaxKv; ++kv)
-          red[(wm * kScorerMaxKv + kv) * kBT + 128 * wn + 16 * nb + li] = part[nb][kv];
+          red[(wm * kScorerMaxKv + kv) * BT + 16 * NB * wn + 16 * nb + li] = part[nb][kv];
     }
     __syncthreads();
-    for (int i = tid; i < kScorerMaxKv * kBT; i += kGemmThreads) {
-      const int kv = i / kBT, tl = i % kBT;
+    for (int i = tid; i < kScorerMaxKv * BT; i += kGemmThreads) {
+      const int kv = i / BT, tl = i % BT;
       const int t = t0 + tl;
       if (kv < p.n_kv && t < p.T)
         p.part[((size_t)ftile * p.n_kv + kv) * p.T + t] =
-            red[kv * kBT + tl] + red[(kScorerMaxKv + kv) * kBT + tl];
+            red[kv * BT + tl] + red[(kScorerMaxKv + kv) * BT + tl];
     }
     return;
   }
 #pragma unroll
-  for (int nb = 0; nb < 8; ++nb) {
-    const int t = t0 + 128 * wn + 16 * nb + li;
+  for (int nb = 0; nb < NB; ++nb) {
+    const int t = t0 + 16 * NB * wn + 16 * nb + li;
     if (t >= p.T) continue;
     if constexpr (EPI == kEpiSwiglu) {
 #pragma unroll
@@ -419,19 +514,75 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmParams p) {
   }
 }
 
+// How the token tiles of one product are cut: `full` tiles of 256 tokens
+// (NB = 8), then tiles of 32 * nb tokens for the rest.  The chip runs one
+// workgroup per CU, so a product takes whole rounds of 256 tiles, and one
+// with fewer or not quite a multiple of them leaves CUs idle: 80 tiles of 256
+// tokens (1256 tokens x 4096 features) take as long as 256.  Smaller tiles
+// cost more per token (a step's copies of the weight slab do not shrink), so
+// the cut is the cheapest by kTiles: the time of one round in units of a
+// 256-token round, measured at K = 4096 to 14336 (O projection of 1256 tokens:
+// 109 us in 80 tiles of 256 tokens, 65 us in 160 of 128, 57 us in 224 of 96,
+// 45 us per round of 64).  A second launch costs its ramp (kSecond).
+struct GemmSplit {
+  int full, nb;
+};
+
+// Rounds of workgroups (one per CU; every XCD gets an eighth of the tiles).
+inline int64_t gemm_rounds(int64_t tiles) { return (tiles + kGemmCus - 1) / kGemmCus; }
+
+inline GemmSplit gemm_split(int64_t T, int64_t nfy) {
+  static const struct { int nb; double cost; } kTiles[] = {{8, 1.0}, {4, 0.54}, {3, 0.50}, {2, 0.43}};
+  constexpr double kSecond = 0.08;
+  const int64_t most = T / 256;  // whole 256-token tiles
+  GemmSplit best{0, 8};
+  double best_cost = (double)gemm_rounds((T + 255) / 256 * nfy);
+  for (const auto& k : kTiles) {
+    if (k.nb == 8) continue;
+    // whole rounds of 256-token tiles first, as many as fit or fewer
+    const int64_t all = gemm_rounds(most * nfy);
+    for (int64_t r = all > 2 ? all - 2 : 0; r <= all; ++r) {
+      const int64_t full = std::min<int64_t>(most, r * kGemmCus / nfy);
+      const int64_t rest = (T - 256 * full + 32 * k.nb - 1) / (32 * k.nb);
+      const double cost = (double)gemm_rounds(full * nfy) + (double)gemm_rounds(rest * nfy) * k.cost +
+                          (full > 0 && rest > 0 ? kSecond : 0.0);
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = GemmSplit{(int)full, k.nb};
+      }
+    }
+  }
+  return best;
+}
+
+template <int XM, int WM, int EPI, int NB, bool EARLY>
+hipError_t launch_gemm_tiles(GemmParams p, int t_begin, int t_end, hipStream_t stream) {
+  p.t_begin = t_begin;
+  p.ntx = (t_end - t_begin + 32 * NB - 1) / (32 * NB);
+  const int64_t tiles = (int64_t)p.ntx * p.nfy;
+  if (tiles == 0) return hipSuccess;
+  const dim3 grid((unsigned)(8 * ((tiles + 7) / 8)));
+  hipLaunchKernelGGL((gemm_kernel<XM, WM, EPI, NB, EARLY>), grid, dim3(NB < 8 ? 2 * kGemmThreads : kGemmThreads),
+                     0, stream, p);
+  return hipGetLastError();
+}
+
 template <int XM, int WM, int EPI>
 hipError_t launch_gemm(GemmParams p, hipStream_t stream) {
   const int per_wg = WM == kWGateUp ? kBF / 2 : kBF;
-  p.ntx = (p.T + kBT - 1) / kBT;
   p.nfy = (p.F + per_wg - 1) / per_wg;
-  p.nbt = (p.ntx + 7) / 8;
-  const int nblocks = ((p.nfy + 3) / 4) * p.nbt;  // blocks of 4 x 8 tiles
-  const dim3 grid((unsigned)(256 * ((nblocks + 7) / 8)));
-  if (p.K >= 8192)
-    hipLaunchKernelGGL((gemm_kernel<XM, WM, EPI, true>), grid, dim3(kGemmThreads), 0, stream, p);
-  else
-    hipLaunchKernelGGL((gemm_kernel<XM, WM, EPI, false>), grid, dim3(kGemmThreads), 0, stream, p);
-  return hipGetLastError();
+  const GemmSplit sp = gemm_split(p.T, p.nfy);
+  const int mid = sp.nb == 8 ? p.T : 256 * sp.full;
+  hipError_t e = hipSuccess;
+  if (p.K >= 8192) e = launch_gemm_tiles<XM, WM, EPI, 8, true>(p, 0, mid, stream);
+  else e = launch_gemm_tiles<XM, WM, EPI, 8, false>(p, 0, mid, stream);
+  if (e != hipSuccess) return e;
+  switch (sp.nb) {
+    case 4: return launch_gemm_tiles<XM, WM, EPI, 4, false>(p, mid, p.T, stream);
+    case 3: return launch_gemm_tiles<XM, WM, EPI, 3, false>(p, mid, p.T, stream);
+    case 2: return launch_gemm_tiles<XM, WM, EPI, 2, false>(p, mid, p.T, stream);
+    default: return hipSuccess;
+  }
 }
 
 }  // namespace
