@@ -2,24 +2,24 @@
 // ArgTop-l_p of the retaining-head scores of every KV head, then the gather
 // K^C = K_h[idx], V^C = V_h[idx].
 //
-// Design.  A grid of (S, n_kv) workgroups; workgroup (c, h) owns the local
-// index range chunk c of KV head h.  Every workgroup of a head first finds
-// the same selection threshold by an MSB-first radix select over all Lb
-// scores (digits of an order-preserving 32-bit key: four of 8 bits here, three
-// of 11, 11 and 10 bits in the register-resident kernel below; the scores of
-// one head are a few hundred KB at most and stay in L2), so no scratch memory,
-// atomics across workgroups or second launch are needed.  It then counts
-// what was selected before its chunk and compacts its chunk in index order
-// (wave ballot + mbcnt prefix counts, a 4-wave LDS scan), which yields the
-// ascending output order and the lower-index-wins tie rule directly.  The
-// selected rows are copied with 16-byte vector loads and stores.
+// Design.  S workgroups per KV head; every one of them first finds the head's
+// selection threshold (the l_p-th largest score, as an order-preserving
+// 32-bit key) and the number selected before each range of indices, then
+// lists and gathers the rows of its own share of the output positions, in
+// index order (ascending output, lower index wins ties), with 16-byte copies.
+// Each repeats the same selection over the head's scores, which stay in L2,
+// so no scratch memory, atomics across workgroups or second launch are
+// needed.  Local blocks up to kRegMaxKeys hold their keys in registers, longer
+// ones stream them.
+#include <math.h>
+
+#include <algorithm>
+#include <type_traits>
+
 #include "apb_internal.h"
 
 namespace apb {
 namespace {
-
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
 
 // Order-preserving map of an fp32 score to an unsigned key: a larger score
 // gives a larger key, -0 maps with +0, NaN maps to 0 (below -inf, whose key
@@ -31,159 +31,30 @@ __device__ __forceinline__ uint32_t score_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Exclusive prefix count of `pred` over the 256 threads of the block, in
-// thread order; also returns the block total.  Uses `scan` (kWaves words).
-__device__ __forceinline__ uint32_t block_exclusive_count(bool pred, uint32_t* scan,
-                                                          uint32_t* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const unsigned long long bal = __ballot(pred);
-  const uint32_t in_wave = __builtin_amdgcn_mbcnt_hi(
-      (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-  if (lane == 0) scan[wave] = (uint32_t)__popcll(bal);
-  __syncthreads();
-  uint32_t before = 0, all = 0;
-  for (int w = 0; w < kWaves; ++w) {
-    const uint32_t c = scan[w];
-    before += (w < wave) ? c : 0u;
-    all += c;
-  }
-  __syncthreads();
-  *total = all;
-  return before + in_wave;
-}
-
-__global__ void __launch_bounds__(kThreads)
-topk_gather_kernel(const float* __restrict__ scores, const uint16_t* __restrict__ k,
-                   const uint16_t* __restrict__ v, int32_t* __restrict__ out_idx,
-                   uint16_t* __restrict__ out_k, uint16_t* __restrict__ out_v,
-                   int La, int Lb, int lp, int head_dim, int chunk) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t scan[kWaves];
-  __shared__ uint32_t sel_digit, sel_above;
-  __shared__ int32_t list_src[kThreads];
-  __shared__ int32_t list_dst[kThreads];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int head = blockIdx.y;
-  const float* s = scores + (size_t)head * Lb;
-
-  // ---- 1. radix select: key T of the lp-th largest score, and how many of
-  //         the scores equal to T are selected (`need`, >= 1).
-  uint32_t prefix = 0u, prefix_mask = 0u, remaining = (uint32_t)lp;
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    hist[tid] = 0u;
-    __syncthreads();
-    for (int i = tid; i < Lb; i += kThreads) {
-      const uint32_t key = score_key(s[i]);
-      if ((key & prefix_mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    if (tid < 64) {
-      // lane L owns bins 4L..4L+3; suffix sums over lanes find the bin
-      // holding the remaining-th largest key.
-      uint32_t c[4], own = 0u;
-      for (int j = 0; j < 4; ++j) { c[j] = hist[4 * lane + j]; own += c[j]; }
-      uint32_t incl = own;  // inclusive suffix sum over lanes >= lane
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = __shfl_down(incl, off);
-        if (lane + off < 64) incl += o;
-      }
-      const uint32_t above_lane = incl - own;
-      if (above_lane < remaining && remaining <= incl) {
-        uint32_t above = above_lane;
-        for (int j = 3; j >= 0; --j) {
-          if (remaining <= above + c[j]) {
-            sel_digit = (uint32_t)(4 * lane + j);
-            sel_above = above;
-            break;
-          }
-          above += c[j];
-        }
-      }
-    }
-    __syncthreads();
-    prefix |= sel_digit << shift;
-    prefix_mask |= 255u << shift;
-    remaining -= sel_above;
-    __syncthreads();
-  }
-  const uint32_t T = prefix;
-  const uint32_t need = remaining;
-
-  // ---- 2. selected elements before this workgroup's chunk.
-  const int c0 = blockIdx.x * chunk;
-  const int c1 = min(Lb, c0 + chunk);
-  if (c0 >= c1) return;
-  uint32_t gt_before = 0u, eq_before = 0u;
-  for (int base = 0; base < c0; base += kThreads) {
-    const int i = base + tid;
-    const uint32_t key = (i < c0) ? score_key(s[i]) : 0u;
-    uint32_t tg, te;
-    block_exclusive_count(i < c0 && key > T, scan, &tg);
-    block_exclusive_count(i < c0 && key == T, scan, &te);
-    gt_before += tg;
-    eq_before += te;
-  }
-
-  // ---- 3. compaction of the chunk in index order + row gather.
-  const int row_chunks = head_dim / 8;  // 16-byte pieces per row
-  const size_t M = (size_t)La + Lb;
-  const uint4* ksrc = reinterpret_cast<const uint4*>(k + (size_t)head * M * head_dim);
-  const uint4* vsrc = reinterpret_cast<const uint4*>(v + (size_t)head * M * head_dim);
-  uint4* kdst = reinterpret_cast<uint4*>(out_k + (size_t)head * lp * head_dim);
-  uint4* vdst = reinterpret_cast<uint4*>(out_v + (size_t)head * lp * head_dim);
-  for (int base = c0; base < c1; base += kThreads) {
-    const int i = base + tid;
-    const uint32_t key = (i < c1) ? score_key(s[i]) : 0u;
-    const bool gt = i < c1 && key > T;
-    const bool eq = i < c1 && key == T;
-    uint32_t tg, te;
-    const uint32_t gx = gt_before + block_exclusive_count(gt, scan, &tg);
-    const uint32_t ex = eq_before + block_exclusive_count(eq, scan, &te);
-    const uint32_t pos = gx + min(ex, need);
-    // pos < lp holds by construction (exactly lp elements are selected); the
-    // test keeps every store in bounds regardless.
-    const bool sel = (gt || (eq && ex < need)) && pos < (uint32_t)lp;
-    uint32_t nsel;
-    const uint32_t slot = block_exclusive_count(sel, scan, &nsel);
-    if (sel) {
-      if (out_idx) out_idx[(size_t)head * lp + pos] = i;
-      list_src[slot] = i;
-      list_dst[slot] = (int32_t)pos;
-    }
-    __syncthreads();
-    const int pieces = (int)nsel * row_chunks;
-    for (int e = tid; e < 2 * pieces; e += kThreads) {
-      const int which = e >= pieces;  // 0: K, 1: V
-      const int ee = e - which * pieces;
-      const int r = ee / row_chunks, ch = ee - r * row_chunks;
-      const size_t src = ((size_t)La + list_src[r]) * row_chunks + ch;
-      const size_t dst = (size_t)list_dst[r] * row_chunks + ch;
-      if (which) vdst[dst] = vsrc[src];
-      else kdst[dst] = ksrc[src];
-    }
-    gt_before += tg;
-    eq_before += te;
-    __syncthreads();
-  }
+// The score of a key that some score has (of -0 and +0: +0); of other keys, a
+// NaN above +inf.
+__device__ __forceinline__ float key_score(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
 }
 
 // ---------------------------------------------------------------------------
-// Register-resident variant for Lb <= 1024 * KPT (up to 32 keys per thread
-// stay in registers without spills; with KPT = 64 the other 32 are staged in
-// LDS, 128 KiB, index-major so that a wave's reads are conflict-free; longer
-// local blocks use the kernel above).  1024 threads; thread t holds the keys
-// of local indices KPT*t .. KPT*t + KPT-1, loaded once with 16-byte vector
-// loads.  The radix select takes three digits of 11, 11 and 10 bits, each
-// counted into one shared 2048-bin histogram (wider digits spread the keys
-// of one wave's atomics over more addresses and save a pass); the selected
-// counts before each thread's range come from a block scan.  Workgroup c of a head then gathers the selected rows whose
-// output positions fall in its share [c*lp/S, (c+1)*lp/S).  Same threshold,
-// same tie rule, same output as the kernel above.
+// Register-resident form, for Lb <= 1024 * KPT.  1024 threads; thread t holds
+// the keys of local indices KPT*t .. KPT*t + KPT-1, loaded once with 16-byte
+// vector loads.  The radix select takes three digits of 11, 11 and 10 bits,
+// each counted into one shared 2048-bin histogram (wider digits spread the
+// keys of one wave's atomics over more addresses and save a pass); the
+// selected counts before each thread's range come from a block scan.
+// Workgroup c of a head then gathers the selected rows whose output positions
+// fall in its share [c*lp/S, (c+1)*lp/S).
 constexpr int kRegThreads = 1024;
 constexpr int kRegWaves = kRegThreads / 64;
 constexpr int kSelBins = 2 * kRegThreads;  // 11-bit digits, two bins per thread
+// Longest block of the register kernel: with 16 keys per thread it takes 13.8 us
+// where the streaming one takes 17.5 (16384 N(0,1) scores, 8 KV heads, l_p =
+// Lb / 8); with 32 keys per thread (and 64, half of them in LDS) it took 21.8
+// against 18.9 us at 20000, 26.2 against 23.7 at 32768, 52.4 against 36.0 at
+// 65536.
+constexpr int kRegMaxKeys = 16 * kRegThreads;
 
 // Inclusive prefix sum over the 64 lanes of a wave: shifts inside each
 // 16-lane row through DPP, then the three row totals taken by readlane.
@@ -205,41 +76,30 @@ topk_gather_reg_kernel(const float* __restrict__ scores, const uint16_t* __restr
                        const uint16_t* __restrict__ v, int32_t* __restrict__ out_idx,
                        uint16_t* __restrict__ out_k, uint16_t* __restrict__ out_v, int La,
                        int Lb, int lp, int head_dim, int share) {
-  constexpr int KREG = KPT < 32 ? KPT : 32;  // keys per thread in registers
-  constexpr int KLDS = KPT - KREG;           // keys per thread in LDS
   __shared__ uint32_t hist[kSelBins];
   __shared__ uint32_t wtot[kRegWaves];
   __shared__ uint32_t wsum_gt[kRegWaves], wsum_eq[kRegWaves];
   __shared__ uint32_t sel_digit, sel_above;
   __shared__ int32_t list_src[1024];
-  __shared__ uint32_t lds_key[KLDS > 0 ? KLDS * kRegThreads : 1];  // [j - KREG][thread]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int head = blockIdx.y;
   const float* s = scores + (size_t)head * Lb;
   const int i0 = KPT * tid;
 
-  // ---- keys in registers (and LDS); indices past Lb are marked invalid
-  uint32_t key[KREG];
-  auto put = [&](int j, uint32_t kv) __attribute__((always_inline)) {
-    if (j < KREG) key[j] = kv;
-    else lds_key[(j - KREG) * kRegThreads + tid] = kv;
-  };
+  // ---- keys in registers; indices past Lb are marked invalid
+  uint32_t key[KPT];
   if (i0 + KPT <= Lb && ((uintptr_t)s & 15u) == 0) {
 #pragma unroll
     for (int j = 0; j < KPT; j += 4) {
       const float4 f = *reinterpret_cast<const float4*>(s + i0 + j);
-      put(j, score_key(f.x)); put(j + 1, score_key(f.y));
-      put(j + 2, score_key(f.z)); put(j + 3, score_key(f.w));
+      key[j] = score_key(f.x); key[j + 1] = score_key(f.y);
+      key[j + 2] = score_key(f.z); key[j + 3] = score_key(f.w);
     }
   } else {
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) put(j, i0 + j < Lb ? score_key(s[i0 + j]) : 0u);
+    for (int j = 0; j < KPT; ++j) key[j] = i0 + j < Lb ? score_key(s[i0 + j]) : 0u;
   }
-  // key j of this thread (each thread reads back only its own LDS slots)
-  auto get = [&](int j) __attribute__((always_inline)) -> uint32_t {
-    return j < KREG ? key[j] : lds_key[(j - KREG) * kRegThreads + tid];
-  };
   const int n_valid = max(0, min(KPT, Lb - i0));
 
   // every share slot is filled below (exactly lp distinct positions are
@@ -258,7 +118,7 @@ topk_gather_reg_kernel(const float* __restrict__ scores, const uint16_t* __restr
     const uint32_t dmask = pass == 2 ? 1023u : 2047u;
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
-      const uint32_t kj = get(j);
+      const uint32_t kj = key[j];
       if (j < n_valid && (kj & prefix_mask) == prefix) atomicAdd(&hist[(kj >> shift) & dmask], 1u);
     }
     __syncthreads();
@@ -295,7 +155,7 @@ topk_gather_reg_kernel(const float* __restrict__ scores, const uint16_t* __restr
   uint32_t n_gt = 0u, n_eq = 0u;
 #pragma unroll
   for (int j = 0; j < KPT; ++j) {
-    const uint32_t kj = get(j);
+    const uint32_t kj = key[j];
     n_gt += (j < n_valid && kj > T) ? 1u : 0u;
     n_eq += (j < n_valid && kj == T) ? 1u : 0u;
   }
@@ -313,7 +173,7 @@ topk_gather_reg_kernel(const float* __restrict__ scores, const uint16_t* __restr
   const int p0 = blockIdx.x * share, p1 = min(lp, p0 + share);
 #pragma unroll
   for (int j = 0; j < KPT; ++j) {
-    const uint32_t kj = get(j);
+    const uint32_t kj = key[j];
     const bool gt = j < n_valid && kj > T;
     const bool eq = j < n_valid && kj == T;
     const uint32_t pos = gt_before + min(eq_before, need);
@@ -348,11 +208,417 @@ topk_gather_reg_kernel(const float* __restrict__ scores, const uint16_t* __restr
   }
 }
 
+// ---------------------------------------------------------------------------
+// Long local blocks (Lb > kRegMaxKeys): the scores are streamed from L2 instead
+// of held, and the threshold's digits are not counted over all of them.  At
+// 131072 power-law scores (l_p = 16384, 8 heads of d = 128) a call takes 68 us,
+// of which the 139 MB it has to move take 27; radix passes over all scores by
+// 256 threads had taken 655.  Bound by the one pass over the scores (its vector
+// instructions: every workgroup of a head repeats it) and then the gather.
+//  1. 4096 evenly spaced sample keys, taken to 22 bits by two histogram
+//     passes, give a bracket [lo, hi] that holds the l_p-th largest key but
+//     for a chance of 1e-4 (four standard deviations of its sample rank to
+//     either side, about 4% of the keys).
+//  2. One pass over the keys (16-byte loads, eight in flight per lane) counts
+//     those above hi by ballot, per chunk of kLongBlock << m keys, and keeps
+//     those inside the bracket, with their chunk, in LDS.  No atomics: scores
+//     like N(0,1) put most keys of a wave into a few bins, and histogram
+//     atomics on one bin take a turn each.
+//  3. A radix select of the kept keys, relative to lo, gives the threshold.
+//     When the bracket misses it or more keys fall inside than LDS holds
+//     (large tied groups at the bracket's edge), a radix select over all keys
+//     takes its place; a bracket of a single key (a tied group) needs neither.
+//  4. A scan over the chunks gives every chunk its output position; the
+//     workgroup reads again only the chunks its share of the output positions
+//     touches, lists their selected rows and gathers them.
+// Same threshold, tie rule and output as the register form.
+constexpr int kLongBlock = 256;      // keys a wave takes at a time (one float4 per lane)
+constexpr int kLongChunks = 1024;    // chunks of a head, one per thread in the scan
+constexpr int kLongCap = 1024;       // bracket keys a wave keeps
+constexpr int kLongBatch = 8;        // blocks a wave loads ahead
+constexpr int kLongSample = 4096;
+constexpr int kLongList = 1024;      // output rows listed at a time
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+struct LongShared {
+  uint32_t hist[2][kSelBins];
+  u32x2 cand[kRegWaves][kLongCap];  // score, chunk
+  uint32_t gt[kLongChunks + 1], eq[kLongChunks + 1];
+  int32_t list_src[kLongList];
+  uint16_t hits[kLongChunks];
+  uint32_t wtot[2][kRegWaves];
+  uint32_t sel_digit[2], sel_above[2];
+  uint32_t n_hits, overflow;
+};
+
+// Of the 2048 bins of hist[0] and hist[1], the bin holding the rank[u]-th
+// largest key of histogram u and the keys above that bin; the bins are
+// cleared.  Every thread calls it with all counts made (no barrier between).
+__device__ __forceinline__ void find_bins(LongShared& sh, const uint32_t (&rank)[2],
+                                          uint32_t (&digit)[2], uint32_t (&above)[2]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __syncthreads();
+  uint32_t c1[2], own[2], incl[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const uint32_t c0 = sh.hist[u][2 * tid];
+    c1[u] = sh.hist[u][2 * tid + 1];
+    sh.hist[u][2 * tid] = 0u;
+    sh.hist[u][2 * tid + 1] = 0u;
+    own[u] = c0 + c1[u];
+    const uint32_t pre = wave_prefix_sum(own[u]);
+    const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63);
+    incl[u] = wt - pre + own[u];  // suffix sum over the lanes >= lane
+    if (lane == 0) sh.wtot[u][wave] = wt;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+#pragma unroll
+    for (int w = 1; w < kRegWaves; ++w) incl[u] += w > wave ? sh.wtot[u][w] : 0u;
+    const uint32_t above_t = incl[u] - own[u];  // keys in the bins above 2t+1
+    if (above_t < rank[u] && rank[u] <= incl[u]) {
+      const bool upper = rank[u] <= above_t + c1[u];
+      sh.sel_digit[u] = (uint32_t)(2 * tid) + (upper ? 1u : 0u);
+      sh.sel_above[u] = above_t + (upper ? 0u : c1[u]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    digit[u] = sh.sel_digit[u];
+    above[u] = sh.sel_above[u];
+  }
+}
+
+// The four scores of this lane in block b of nb (indices kLongBlock * b + 4 * lane
+// ..); past the end +0 (such keys are never counted).
+__device__ __forceinline__ f32x4 load_block(const float* s, int b, int nb, int Lb, bool vec) {
+  const int lane = threadIdx.x & 63;
+  f32x4 f = {0.f, 0.f, 0.f, 0.f};
+  if (b < nb) {
+    const int i0 = b * kLongBlock + 4 * lane, left = Lb - i0;
+    if (vec && left >= 4) {
+      f = *reinterpret_cast<const f32x4*>(s + i0);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j < left) f[j] = s[i0 + j];
+    }
+  }
+  return f;
+}
+
+// Calls body(block, scores, valid) for every block of this wave (wave, wave +
+// 16, ...), with this lane's four scores, of which the first `valid` count;
+// kLongBatch blocks' loads at a time and the next batch's in flight behind them.
+template <typename Body>
+__device__ __forceinline__ void for_blocks(const float* s, int Lb, Body body) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (Lb + kLongBlock - 1) / kLongBlock;
+  const bool vec = ((uintptr_t)s & 15u) == 0;
+  f32x4 next[kLongBatch];
+#pragma unroll
+  for (int u = 0; u < kLongBatch; ++u) next[u] = load_block(s, wave + kRegWaves * u, nb, Lb, vec);
+  for (int b0 = wave; b0 < nb; b0 += kRegWaves * kLongBatch) {
+    f32x4 cur[kLongBatch];
+#pragma unroll
+    for (int u = 0; u < kLongBatch; ++u) {
+      cur[u] = next[u];
+      next[u] = load_block(s, b0 + kRegWaves * (kLongBatch + u), nb, Lb, vec);
+    }
+#pragma unroll
+    for (int u = 0; u < kLongBatch; ++u) {
+      const int b = b0 + kRegWaves * u;
+      if (b < nb) body(b, cur[u], Lb - (b * kLongBlock + 4 * lane));
+    }
+  }
+}
+
+__global__ void __launch_bounds__(kRegThreads)
+topk_gather_long_kernel(const float* __restrict__ scores, const uint16_t* __restrict__ k,
+                        const uint16_t* __restrict__ v, int32_t* __restrict__ out_idx,
+                        uint16_t* __restrict__ out_k, uint16_t* __restrict__ out_v, int La,
+                        int Lb, int lp, int n_kv, int head_dim, int share, int chunk_shift) {
+  __shared__ LongShared sh;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // consecutive workgroups go to different XCDs: with n_kv = 8 a head's scores
+  // stay in one L2
+  const int head = blockIdx.x % n_kv;
+  const float* s = scores + (size_t)head * Lb;
+  const int nb = (Lb + kLongBlock - 1) / kLongBlock;
+  const int nchunks = ((nb - 1) >> chunk_shift) + 1;
+
+  for (int i = tid; i < 2 * kSelBins; i += kRegThreads) (&sh.hist[0][0])[i] = 0u;
+  for (int i = tid; i <= kLongChunks; i += kRegThreads) sh.gt[i] = sh.eq[i] = 0u;
+  if (tid == 0) sh.overflow = 0u;
+
+  // ---- 1. the bracket, from the sample
+  uint32_t smp[kLongSample / kRegThreads];
+#pragma unroll
+  for (int j = 0; j < kLongSample / kRegThreads; ++j)
+    smp[j] = score_key(s[(size_t)((uint64_t)(j * kRegThreads + tid) * (uint64_t)Lb / kLongSample)]);
+  __syncthreads();
+  const float mean = (float)lp / (float)Lb * kLongSample;
+  const float dev = 4.f * sqrtf(fmaxf(mean * (1.f - mean / kLongSample), 0.f)) + 4.f;
+  uint32_t rank[2] = {(uint32_t)max(1, (int)(mean - dev)),
+                      (uint32_t)min(kLongSample, (int)(mean + dev) + 1)};
+  uint32_t digit[2], above[2], top[2];
+  const uint32_t first_rank = rank[0], last_rank = rank[1];
+#pragma unroll
+  for (int j = 0; j < kLongSample / kRegThreads; ++j) {
+    atomicAdd(&sh.hist[0][smp[j] >> 21], 1u);
+    atomicAdd(&sh.hist[1][smp[j] >> 21], 1u);
+  }
+  find_bins(sh, rank, digit, above);
+  top[0] = digit[0];
+  top[1] = digit[1];
+  rank[0] -= above[0];
+  rank[1] -= above[1];
+#pragma unroll
+  for (int j = 0; j < kLongSample / kRegThreads; ++j)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (smp[j] >> 21 == top[u]) atomicAdd(&sh.hist[u][(smp[j] >> 10) & 2047u], 1u);
+  find_bins(sh, rank, digit, above);
+  // to 22 bits: the upper edge of hi's bin, the lower edge of lo's; an end of
+  // the sample leaves its side open.  A single tied key shows as equal sample
+  // keys: its whole 22-bit bin may hold other keys, which the select sorts out.
+  uint32_t hi = first_rank <= 1 ? 0xffffffffu : (top[0] << 21 | digit[0] << 10 | 1023u);
+  uint32_t lo = last_rank >= kLongSample ? 0u : (top[1] << 21 | digit[1] << 10);
+
+  // The pass compares the scores themselves, which agrees with the keys once
+  // no bound lies between -0 and +0 or between NaN and -inf (NaN compares
+  // false with all, so it is neither above nor inside; if the threshold is
+  // down there, the counts below say so).
+  const bool in_nan = hi < 0x007fffffu;  // a threshold that only the keys order
+  if (hi == 0x7fffffffu) hi = 0x80000000u;
+  hi = max(hi, 0x007fffffu);
+  lo = max(lo, 0x007fffffu);
+  const float hi_f = key_score(hi), lo_f = key_score(lo);
+
+  // ---- 2. one pass: keys above hi per chunk, bracket keys kept
+  uint32_t kept = 0u;  // this wave's bracket keys
+  for_blocks(s, in_nan ? 0 : Lb, [&](int b, f32x4 f, int valid) __attribute__((always_inline)) {
+    const uint32_t chunk = (uint32_t)(b >> chunk_shift);
+    const bool full = (b + 1) * kLongBlock <= Lb;
+    uint32_t n_gt = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      unsigned long long above_m = __ballot(f[j] > hi_f), m = __ballot(f[j] >= lo_f);
+      if (!full) {
+        const unsigned long long ok = __ballot(j < valid);
+        above_m &= ok;
+        m &= ok;
+      }
+      m &= ~above_m;
+      n_gt += (uint32_t)__popcll(above_m);
+      const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+          (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, kept));
+      if ((m >> lane & 1) && at < (uint32_t)kLongCap)
+        sh.cand[wave][at] = u32x2{__float_as_uint(f[j]), chunk};
+      kept += (uint32_t)__popcll(m);
+    }
+    if (lane == 0 && n_gt) atomicAdd(&sh.gt[chunk], n_gt);
+  });
+  if (lane == 0) {
+    sh.wtot[0][wave] = kept;
+    if (kept > (uint32_t)kLongCap) sh.overflow = 1u;
+  }
+  __syncthreads();
+  uint32_t n_in = 0u;
+  for (int w = 0; w < kRegWaves; ++w) n_in += sh.wtot[0][w];
+  const uint32_t my_gt = sh.gt[tid];  // kLongChunks == kRegThreads
+  const bool overflow = sh.overflow != 0u;
+  __syncthreads();
+  {
+    const uint32_t pre = wave_prefix_sum(my_gt);
+    if (lane == 63) sh.wtot[1][wave] = pre;
+  }
+  __syncthreads();
+  uint32_t n_above = 0u;
+  for (int w = 0; w < kRegWaves; ++w) n_above += sh.wtot[1][w];
+  __syncthreads();
+
+  // ---- 3. threshold key T and how many of the keys equal to it are selected
+  const bool kept_all = !overflow && n_above < (uint32_t)lp && (uint32_t)lp <= n_above + n_in;
+  if (!kept_all) {
+    lo = 0u;
+    hi = 0xffffffffu;
+    sh.gt[tid] = 0u;
+  }
+  uint32_t remaining = kept_all ? (uint32_t)lp - n_above : (uint32_t)lp;
+  int bits = lo == hi ? 0 : 32 - __builtin_clz(hi - lo);
+  uint32_t prefix = 0u;  // of key - lo, its bits from `bits` up
+  const uint32_t mine = min(kept, (uint32_t)kLongCap);
+  while (bits > 0) {
+    const int w = min(11, bits), above_bits = bits;
+    bits -= w;
+    // (A shift by 32 is not defined; then every key counts.)  With ties, the
+    // lanes of a wave that share the first lane's bin, then those that share the
+    // next one's, add together: their atomics would take a turn each.
+    auto count = [&](uint32_t d, bool valid, auto ties) __attribute__((always_inline)) {
+      const uint32_t bin = d >> bits & ((1u << w) - 1u);
+      unsigned long long todo = __ballot(valid && (above_bits == 32 || d >> above_bits == prefix));
+#pragma unroll
+      for (int round = 0; round < (decltype(ties)::value ? 2 : 0); ++round) {
+        if (todo == 0) break;
+        const int leader = __builtin_ctzll(todo);
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)bin, leader);
+        const unsigned long long same = __ballot(bin == first) & todo;
+        if (lane == leader) atomicAdd(&sh.hist[0][first], (uint32_t)__popcll(same));
+        todo &= ~same;
+      }
+      if (todo >> lane & 1) atomicAdd(&sh.hist[0][bin], 1u);
+    };
+    auto count_kept = [&](auto ties) __attribute__((always_inline)) {
+      for (uint32_t i = 0; i < mine; i += 64) {
+        const bool valid = i + lane < mine;
+        count(valid ? score_key(__uint_as_float(sh.cand[wave][i + lane][0])) - lo : 0u, valid, ties);
+      }
+    };
+    if (kept_all && n_in <= (uint32_t)Lb / 8) {  // the bracket alone holds about 4%
+      count_kept(std::false_type{});
+    } else if (kept_all) {
+      count_kept(std::true_type{});
+    } else {
+      for_blocks(s, Lb, [&](int, f32x4 f, int valid) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) count(score_key(f[j]) - lo, j < valid, std::true_type{});
+      });
+    }
+    rank[0] = remaining;
+    rank[1] = 0u;  // unused: no bin matches
+    find_bins(sh, rank, digit, above);
+    prefix = prefix << w | digit[0];
+    remaining -= above[0];
+  }
+  const uint32_t T = lo + prefix;
+  const uint32_t need = remaining;
+
+  // ---- 4. keys above and equal to T per chunk, then before every chunk
+  __syncthreads();
+  if (kept_all) {
+    for (uint32_t i = lane; i < mine; i += 64) {
+      const u32x2 c = sh.cand[wave][i];
+      const uint32_t key = score_key(__uint_as_float(c[0]));
+      if (key > T) atomicAdd(&sh.gt[c[1]], 1u);
+      else if (key == T) atomicAdd(&sh.eq[c[1]], 1u);
+    }
+  } else {
+    for_blocks(s, Lb, [&](int b, f32x4 f, int valid) __attribute__((always_inline)) {
+      uint32_t n_gt = 0u, n_eq = 0u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t key = score_key(f[j]);
+        n_gt += (uint32_t)__popcll(__ballot(j < valid && key > T));
+        n_eq += (uint32_t)__popcll(__ballot(j < valid && key == T));
+      }
+      if (lane == 0) {
+        const uint32_t chunk = (uint32_t)(b >> chunk_shift);
+        if (n_gt) atomicAdd(&sh.gt[chunk], n_gt);
+        if (n_eq) atomicAdd(&sh.eq[chunk], n_eq);
+      }
+    });
+  }
+  __syncthreads();
+  {
+    const uint32_t g = sh.gt[tid], e = sh.eq[tid];
+    uint32_t xg = wave_prefix_sum(g), xe = wave_prefix_sum(e);
+    if (lane == 63) {
+      sh.wtot[0][wave] = xg;
+      sh.wtot[1][wave] = xe;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kRegWaves - 1; ++w) {
+      xg += w < wave ? sh.wtot[0][w] : 0u;
+      xe += w < wave ? sh.wtot[1][w] : 0u;
+    }
+    sh.gt[tid + 1] = xg;  // element 0 stays 0 below
+    sh.eq[tid + 1] = xe;
+    if (tid == 0) sh.gt[0] = sh.eq[0] = 0u;
+  }
+
+  // ---- 5. this workgroup's share of the output positions, a list at a time
+  const int p_begin = (int)(blockIdx.x / n_kv) * share, p_end = min(lp, p_begin + share);
+  const int row_chunks = head_dim / 8;  // 16-byte pieces per row
+  const size_t M = (size_t)La + Lb;
+  const u32x4* ksrc = reinterpret_cast<const u32x4*>(k + (size_t)head * M * head_dim);
+  const u32x4* vsrc = reinterpret_cast<const u32x4*>(v + (size_t)head * M * head_dim);
+  u32x4* kdst = reinterpret_cast<u32x4*>(out_k + (size_t)head * lp * head_dim);
+  u32x4* vdst = reinterpret_cast<u32x4*>(out_v + (size_t)head * lp * head_dim);
+  for (int p0 = p_begin; p0 < p_end; p0 += kLongList) {
+    const int p1 = min(p_end, p0 + kLongList);
+    if (tid == 0) sh.n_hits = 0u;
+    // every slot is filled below (exactly lp positions are selected); -1
+    // marks a slot as empty for the gather regardless
+    sh.list_src[tid] = -1;
+    __syncthreads();
+    if (tid < nchunks) {
+      const uint32_t first = sh.gt[tid] + min(sh.eq[tid], need);
+      const uint32_t last = sh.gt[tid + 1] + min(sh.eq[tid + 1], need);
+      if (first < (uint32_t)p1 && last > (uint32_t)p0 && first < last)
+        sh.hits[atomicAdd(&sh.n_hits, 1u)] = (uint16_t)tid;
+    }
+    __syncthreads();
+    const int n_hits = (int)sh.n_hits;
+    for (int h = wave; h < n_hits; h += kRegWaves) {
+      const int chunk = sh.hits[h];
+      uint32_t n_gt = sh.gt[chunk], n_eq = sh.eq[chunk];
+      const int c0 = (chunk << chunk_shift) * kLongBlock;
+      const int c1 = min(Lb, c0 + (kLongBlock << chunk_shift));
+      for (int base = c0; base < c1; base += 4 * 64) {
+        float f[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[j] = base + 64 * j + lane < c1 ? s[base + 64 * j + lane] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int i = base + 64 * j + lane;
+          const uint32_t key = score_key(f[j]);
+          const unsigned long long mg = __ballot(i < c1 && key > T);
+          const unsigned long long me = __ballot(i < c1 && key == T);
+          const bool gt = i < c1 && key > T, eq = i < c1 && key == T;
+          const uint32_t rg = n_gt + __builtin_amdgcn_mbcnt_hi(
+                                         (uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, 0u));
+          const uint32_t re = n_eq + __builtin_amdgcn_mbcnt_hi(
+                                         (uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0u));
+          const uint32_t pos = rg + min(re, need);
+          if ((gt || (eq && re < need)) && pos >= (uint32_t)p0 && pos < (uint32_t)p1) {
+            sh.list_src[pos - p0] = i;
+            if (out_idx) out_idx[(size_t)head * lp + pos] = i;
+          }
+          n_gt += (uint32_t)__popcll(mg);
+          n_eq += (uint32_t)__popcll(me);
+        }
+      }
+    }
+    __syncthreads();
+    const int pieces = (p1 - p0) * row_chunks;  // per tensor
+    for (int e = tid; e < pieces; e += kRegThreads) {
+      const int r = e / row_chunks, ch = e - r * row_chunks;
+      const int li = sh.list_src[r];
+      if (li < 0 || li >= Lb) continue;
+      const size_t src = ((size_t)La + li) * row_chunks + ch;
+      const size_t dst = (size_t)(p0 + r) * row_chunks + ch;
+      const u32x4 kx = ksrc[src], vx = vsrc[src];
+      kdst[dst] = kx;
+      vdst[dst] = vx;
+    }
+    __syncthreads();
+  }
+}
+
 }  // namespace
 
 hipError_t launch_compress(const CompressArgs& a, hipStream_t stream) {
   if (a.lp == 0) return hipSuccess;
-  if (a.Lb <= kRegThreads * 64) {
+  if (a.Lb <= kRegMaxKeys) {
     // a share of at most 1024 output rows per workgroup, about 64 rows each
     // for the gather, at most 32 workgroups per head
     int groups = (a.lp + 63) / 64;
@@ -366,25 +632,22 @@ hipError_t launch_compress(const CompressArgs& a, hipStream_t stream) {
     if (a.Lb <= kRegThreads * 4)
       hipLaunchKernelGGL(topk_gather_reg_kernel<4>, grid, dim3(kRegThreads), 0, stream, a.scores,
                          a.k, a.v, a.idx, a.out_k, a.out_v, a.La, a.Lb, a.lp, a.head_dim, share);
-    else if (a.Lb <= kRegThreads * 16)
-      hipLaunchKernelGGL(topk_gather_reg_kernel<16>, grid, dim3(kRegThreads), 0, stream, a.scores,
-                         a.k, a.v, a.idx, a.out_k, a.out_v, a.La, a.Lb, a.lp, a.head_dim, share);
-    else if (a.Lb <= kRegThreads * 32)
-      hipLaunchKernelGGL(topk_gather_reg_kernel<32>, grid, dim3(kRegThreads), 0, stream, a.scores,
-                         a.k, a.v, a.idx, a.out_k, a.out_v, a.La, a.Lb, a.lp, a.head_dim, share);
     else
-      hipLaunchKernelGGL(topk_gather_reg_kernel<64>, grid, dim3(kRegThreads), 0, stream, a.scores,
+      hipLaunchKernelGGL(topk_gather_reg_kernel<16>, grid, dim3(kRegThreads), 0, stream, a.scores,
                          a.k, a.v, a.idx, a.out_k, a.out_v, a.La, a.Lb, a.lp, a.head_dim, share);
     return hipGetLastError();
   }
-  // Enough workgroups per head to spread the gather over the chip, each
-  // owning at least 1024 local indices.
-  int splits = a.Lb / 1024;
-  splits = splits < 1 ? 1 : (splits > 32 ? 32 : splits);
-  const int chunk = (a.Lb + splits - 1) / splits;
-  dim3 grid(splits, a.n_kv);
-  hipLaunchKernelGGL(topk_gather_kernel, grid, dim3(kThreads), 0, stream, a.scores, a.k, a.v,
-                     a.idx, a.out_k, a.out_v, a.La, a.Lb, a.lp, a.head_dim, chunk);
+  // about 64 rows or more per workgroup for the gather, at most a workgroup per
+  // CU over all heads (a head's workgroups each repeat its select)
+  int groups = a.lp / 64 + (a.lp % 64 != 0);
+  groups = std::min(groups, std::max(1, 256 / a.n_kv));
+  const int share = a.lp / groups + (a.lp % groups != 0);
+  const int blocks = (a.Lb + kLongBlock - 1) / kLongBlock;
+  int chunk_shift = 0;
+  while (((blocks - 1) >> chunk_shift) >= kLongChunks) ++chunk_shift;
+  hipLaunchKernelGGL(topk_gather_long_kernel, dim3((unsigned)(groups * a.n_kv)), dim3(kRegThreads), 0,
+                     stream, a.scores, a.k, a.v, a.idx, a.out_k, a.out_v, a.La, a.Lb, a.lp, a.n_kv,
+                     a.head_dim, share, chunk_shift);
   return hipGetLastError();
 }
 
