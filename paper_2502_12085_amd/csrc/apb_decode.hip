@@ -16,13 +16,15 @@
 // partials a third of the step's bytes, write it in fp16 against a per-row
 // power-of-two scale (every value within 2^-11 of the row's largest).  Few rows per KV
 // head (one generated token): one-wave workgroups of one 32-row block each.
-// Many rows (the question tokens): eight-wave workgroups that share each
+// 65 to 127 rows: two groups of four waves, each group sharing its key blocks.
+// More rows (the question tokens): eight-wave workgroups that share each
 // 128-key K/V tile among 256 rows and alternate MFMA and softmax phases
 // between two wave groups, on the prefill kernel's schedule.
 //  * S^T = K Q^T on v_mfma_f32_32x32x16_bf16 (32 keys on M, 32 rows on N).
 //  * K and V are copied HBM -> LDS with global_load_lds_dwordx4 into
 //    XOR-swizzled row-major tiles while earlier ones are computed (32-key
-//    blocks through a three-stage ring for one wave; 128-key tiles through
+//    blocks through a three-stage ring for one wave, a four-stage one per group
+//    of four; 128-key tiles through
 //    two-stage rings, K and V copied in different phases, for eight).  K is
 //    read back with
 //    ds_read_b128 as the A operand of S^T; V is read back transposed with
@@ -56,7 +58,8 @@ typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 constexpr int kRows = 32;   // rows per workgroup (the MFMA N side)
 constexpr int kKeys = 32;   // keys per MFMA block (the MFMA M side)
 constexpr int kWgPerCu = 3; // one-wave workgroups per CU (LDS: 3 x 48 KiB at d = 128)
-constexpr int kRing = 3;    // LDS stages of K and V blocks per workgroup
+constexpr int kRing = 3;    // LDS stages of K and V blocks per one-wave workgroup
+constexpr int kGroupRing = 4;  // LDS stages of each of the two groups of a four-wave workgroup
 constexpr float kSumLimit = 8192.f;  // lazy rescale: largest block row-half sum against a stale max
 
 struct DecParams {
@@ -129,11 +132,17 @@ __device__ __forceinline__ const uint16_t* kv_row(const DecParams& p, const uint
 // kernel) and its QK products run as four independent accumulator chains.
 constexpr int kPingPongKB = 4;
 
-// Few rows per KV head (one generated token): a one-wave workgroup owns the
-// 32-row block blockIdx.z (kWgPerCu of them share a CU's LDS) and streams
-// its split's 32-key blocks through its own ring.
-template <int D>
-__global__ void __launch_bounds__(64) decode_partial_kernel(DecParams p) {
+// Fewer rows per KV head, up to 32 * W.  W = 1 (one generated token, and up to 64
+// rows as two workgroups): a one-wave workgroup owns the 32-row block blockIdx.z
+// and streams its split's 32-key blocks through its own ring of RING LDS stages
+// (kWgPerCu workgroups share a CU's LDS).  W = 4 (some tokens): KS groups of four
+// waves take the split's blocks in turn, each group through a ring of its own;
+// wave w of a group owns the 32-row block w, and a group's waves share its
+// copies, two copying K and two V (a wave without rows only copies).  One barrier
+// per block orders copies and reads; the groups' results meet in LDS, so that a
+// split is one partial.
+template <int D, int W, int KS, int RING>
+__global__ void __launch_bounds__(64 * W * KS, KS) decode_partial_kernel(DecParams p) {
   constexpr int BK = kKeys;                  // keys per ring block
   constexpr int NKC = D / 16;                // MFMA k-steps over head_dim
   constexpr int NDB = D / 32;                // 32-dim blocks of O^T
@@ -141,14 +150,16 @@ __global__ void __launch_bounds__(64) decode_partial_kernel(DecParams p) {
   constexpr int PIECES = BK * D / 512;       // 1 KiB copies per K or V tile
   static_assert(PIECES == 4 || PIECES == 8, "copy unrolling below");
   constexpr int ROWS_PER_PIECE = 512 / D;
-  constexpr int CPW = 2 * PIECES;            // copies per block
+  constexpr int CPW = 2 * PIECES / W;        // copies per wave per block
   // 256-byte aligned: operand addresses XOR step bits into the low byte of
   // a stage base plus lane offset
-  __shared__ __attribute__((aligned(256))) uint16_t k_lds[kRing][BK * D];
-  __shared__ __attribute__((aligned(256))) uint16_t v_lds[kRing][BK * D];
+  __shared__ __attribute__((aligned(256))) uint16_t k_lds[KS * RING][BK * D];
+  __shared__ __attribute__((aligned(256))) uint16_t v_lds[KS * RING][BK * D];
 
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
-  const int split = blockIdx.x, kvh = blockIdx.y, rb = blockIdx.z;
+  const int wave_id = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = wave_id % W, grp = wave_id / W;
+  const int split = blockIdx.x, kvh = blockIdx.y, rb = blockIdx.z * W + wave;
   const int Ltot = p.Lc + (p.append ? p.n_new : 0);
   const int nblk = (Ltot + BK - 1) / BK;
   const int b0 = split * p.blocks_per_split;
@@ -194,58 +205,79 @@ __global__ void __launch_bounds__(64) decode_partial_kernel(DecParams p) {
   // (less the piece's KiB) are fixed per lane.  A block that straddles the
   // cache end or the last key looks its rows up one by one (rows past the
   // last key repeat it and are masked).
-  uint32_t k_off[PIECES], v_off[PIECES];
-#pragma unroll
-  for (int j = 0; j < PIECES; ++j) {
-    const int row = j * ROWS_PER_PIECE + cp_row0;
-    // the instruction offset is 13-bit signed: pieces 4..7 use M0 + 4 KiB
-    k_off[j] = 2u * (uint32_t)(row * D + 8 * (cp_slot ^ k_swz<D>(row))) - 1024u * (j & 3);
-    v_off[j] = 2u * (uint32_t)(row * D + 8 * (cp_slot ^ v_swz<D>(row))) - 1024u * (j & 3);
-  }
-  auto load_block = [&](int b, int buf) __attribute__((always_inline)) {
-    const int c0 = b * BK;
-    const uint32_t kd = __builtin_amdgcn_readfirstlane(lds_offset(k_lds[buf]));
-    const uint32_t vd = __builtin_amdgcn_readfirstlane(lds_offset(v_lds[buf]));
-    const bool in_cache = c0 + BK <= p.Lc;
-    const bool in_new = c0 >= p.Lc && c0 + BK <= Ltot;
-    if (in_cache || in_new) {
-      const size_t r0 = in_cache ? (size_t)kvh * p.Lc + c0 : (size_t)kvh * p.n_new + (c0 - p.Lc);
-      const uint16_t* kb = (in_cache ? p.kc : p.kn) + r0 * D;
-      const uint16_t* vb = (in_cache ? p.vc : p.vn) + r0 * D;
 #define APB_DEC_PIECE(J, OFFS, BASE)                                                     \
   asm volatile("global_load_lds_dwordx4 %0, %1 offset:" #J ::"v"(OFFS[(J) / 1024 + q4]), \
                "s"(BASE)                                                                 \
                : "memory")
+  // this wave's pieces of a tile: all of both (W = 1), or PPW of K or V
+  constexpr int PPW = W == 1 ? PIECES : CPW;
+  const bool copies_v = W > 1 && wave >= W / 2;
+  const int piece0 = W == 1 ? 0 : (wave % (W / 2 > 0 ? W / 2 : 1)) * PPW;
+  uint32_t k_off[PPW], v_off[W == 1 ? PPW : 1];
 #pragma unroll
-      for (int q4 = 0; q4 < PIECES; q4 += 4) {
-        asm volatile("s_mov_b32 m0, %0" ::"s"(kd + 1024u * q4) : "memory");
+  for (int j = 0; j < PPW; ++j) {
+    const int row = (piece0 + j) * ROWS_PER_PIECE + cp_row0;
+    // the instruction offset is 13-bit signed: pieces 4..7 use M0 + 4 KiB
+    k_off[j] = 2u * (uint32_t)(row * D + 8 * (cp_slot ^ (copies_v ? v_swz<D>(row) : k_swz<D>(row)))) -
+               1024u * (j & 3);
+    if constexpr (W == 1)
+      v_off[j] = 2u * (uint32_t)(row * D + 8 * (cp_slot ^ v_swz<D>(row))) - 1024u * (j & 3);
+  }
+  auto load_block = [&](int b, int buf) __attribute__((always_inline)) {
+    const int c0 = b * BK;
+    const uint32_t kd = __builtin_amdgcn_readfirstlane(
+        lds_offset(copies_v ? v_lds[buf] : k_lds[buf]) + 1024u * piece0);
+    const uint32_t vd = __builtin_amdgcn_readfirstlane(lds_offset(v_lds[buf]));
+    const bool in_cache = c0 + BK <= p.Lc;
+    const bool in_new = c0 >= p.Lc && c0 + BK <= Ltot;
+    const uint16_t* k_cache = copies_v ? p.vc : p.kc;
+    const uint16_t* k_fresh = copies_v ? p.vn : p.kn;
+    if (in_cache || in_new) {
+      const size_t r0 = in_cache ? (size_t)kvh * p.Lc + c0 : (size_t)kvh * p.n_new + (c0 - p.Lc);
+      const uint16_t* kb = (in_cache ? k_cache : k_fresh) + r0 * D;
+      const uint16_t* vb = (in_cache ? p.vc : p.vn) + r0 * D;
+      if constexpr (PPW == 2) {
+        constexpr int q4 = 0;
+        asm volatile("s_mov_b32 m0, %0" ::"s"(kd) : "memory");
         APB_DEC_PIECE(0, k_off, kb);
         APB_DEC_PIECE(1024, k_off, kb);
-        APB_DEC_PIECE(2048, k_off, kb);
-        APB_DEC_PIECE(3072, k_off, kb);
-        asm volatile("s_mov_b32 m0, %0" ::"s"(vd + 1024u * q4) : "memory");
-        APB_DEC_PIECE(0, v_off, vb);
-        APB_DEC_PIECE(1024, v_off, vb);
-        APB_DEC_PIECE(2048, v_off, vb);
-        APB_DEC_PIECE(3072, v_off, vb);
+      } else {
+#pragma unroll
+        for (int q4 = 0; q4 < PPW; q4 += 4) {
+          asm volatile("s_mov_b32 m0, %0" ::"s"(kd + 1024u * q4) : "memory");
+          APB_DEC_PIECE(0, k_off, kb);
+          APB_DEC_PIECE(1024, k_off, kb);
+          APB_DEC_PIECE(2048, k_off, kb);
+          APB_DEC_PIECE(3072, k_off, kb);
+          if constexpr (W == 1) {
+            asm volatile("s_mov_b32 m0, %0" ::"s"(vd + 1024u * q4) : "memory");
+            APB_DEC_PIECE(0, v_off, vb);
+            APB_DEC_PIECE(1024, v_off, vb);
+            APB_DEC_PIECE(2048, v_off, vb);
+            APB_DEC_PIECE(3072, v_off, vb);
+          }
+        }
       }
-#undef APB_DEC_PIECE
     } else {
 #pragma unroll
-      for (int j = 0; j < PIECES; ++j) {
-        const int row = j * ROWS_PER_PIECE + cp_row0;
+      for (int j = 0; j < PPW; ++j) {
+        const int row = (piece0 + j) * ROWS_PER_PIECE + cp_row0;
         const int c = min(c0 + row, Ltot - 1);
-        const uint16_t* ks = kv_row<D>(p, p.kc, p.kn, kvh, c) + 8 * (cp_slot ^ k_swz<D>(row));
-        const uint16_t* vs = kv_row<D>(p, p.vc, p.vn, kvh, c) + 8 * (cp_slot ^ v_swz<D>(row));
+        const int swz = copies_v ? v_swz<D>(row) : k_swz<D>(row);
+        const uint16_t* ks = kv_row<D>(p, k_cache, k_fresh, kvh, c) + 8 * (cp_slot ^ swz);
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(ks),
                      "s"(kd + 1024u * j)
                      : "memory");
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(vs),
-                     "s"(vd + 1024u * j)
-                     : "memory");
+        if constexpr (W == 1) {
+          const uint16_t* vs = kv_row<D>(p, p.vc, p.vn, kvh, c) + 8 * (cp_slot ^ v_swz<D>(row));
+          asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(vs),
+                       "s"(vd + 1024u * j)
+                       : "memory");
+        }
       }
     }
   };
+#undef APB_DEC_PIECE
 
   f32x16 oacc[NDB];
 #pragma unroll
@@ -254,17 +286,25 @@ __global__ void __launch_bounds__(64) decode_partial_kernel(DecParams p) {
     for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
-  // three-stage ring: blocks b+1 and b+2 fly while block b is computed
+  // The group's blocks are b0 + grp, b0 + grp + KS, ...; the next RING-1 of them
+  // fly while one is computed.
 #pragma unroll
-  for (int i = 0; i < kRing - 1; ++i)
-    if (b0 + i < b1) load_block(b0 + i, i);
-  static_assert(CPW * (kRing - 2) <= 63, "vmcnt immediate range");
-  for (int b = b0; b < b1; ++b) {
-    const int buf = (b - b0) % kRing;
-    // block b has landed once only the blocks issued after it are outstanding
-    wait_blocks<CPW, kRing - 2>(min(b1 - 1 - b, kRing - 2));
-    // block b+kRing-1 reuses the stage of block b-1, whose reads are done
-    if (b + kRing - 1 < b1) load_block(b + kRing - 1, (b - b0 + kRing - 1) % kRing);
+  for (int i = 0; i < RING - 1; ++i)
+    if (b0 + grp + i * KS < b1) load_block(b0 + grp + i * KS, grp * RING + i);
+  static_assert(CPW * (RING - 2) <= 63, "vmcnt immediate range");
+  const bool has_rows = W == 1 || rb * kRows < p.R;
+  for (int b = b0 + grp; b - grp < b1; b += KS) {  // as many turns in every group
+    const int i = (b - grp - b0) / KS;
+    const int buf = grp * RING + i % RING;
+    // block b has landed once only the group's later blocks are outstanding
+    wait_blocks<CPW, RING - 2>(min(max(b1 - 1 - b, 0) / KS, RING - 2));
+    // W > 1: every wave's copies of this turn's block have landed, and every
+    // wave's reads of the last turn's are done
+    if constexpr (W > 1) asm volatile("s_barrier" ::: "memory");
+    // the block RING-1 turns on reuses the last turn's stage, whose reads are done
+    if (b + (RING - 1) * KS < b1) load_block(b + (RING - 1) * KS, grp * RING + (i + RING - 1) % RING);
+    if constexpr (W > 1)
+      if (!has_rows || b >= b1) continue;
     // The operand reads of each product are issued together ahead of its
     // MFMAs (the scheduling barriers stop the compiler from re-serialising
     // read, wait, MFMA): the K operands, the QK MFMAs, the V operands (read
@@ -364,8 +404,37 @@ __global__ void __launch_bounds__(64) decode_partial_kernel(DecParams p) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   }
 
+  float l_tot = l_run + half_swap(l_run);
+  if constexpr (KS > 1) {
+    // the second group's O, running max and sum through LDS (the rings are done
+    // with), rescaled to the larger max of the two
+    static_assert(KS == 2 && NDB * 16 * 64 * W * 2 <= KS * RING * BK * D, "merge buffer");
+    float* const o_lds = reinterpret_cast<float*>(&k_lds[0][0]) + wave * (NDB * 16 * 64) + lane;
+    float* const m_lds = reinterpret_cast<float*>(&v_lds[0][0]) + wave * 128 + lane;
+    asm volatile("s_barrier" ::: "memory");
+    if (grp == 1) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o_lds[64 * (16 * db + r)] = oacc[db][r];
+      m_lds[0] = m_run;
+      m_lds[64] = l_tot;
+    }
+    __syncthreads();
+    if (grp == 1) return;
+    const float m1 = m_lds[0], l1 = m_lds[64];
+    const float m = fmaxf(m_run, m1);
+    const float a0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
+    const float a1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        oacc[db][r] = oacc[db][r] * a0 + o_lds[64 * (16 * db + r)] * a1;
+    m_run = m;
+    l_tot = l_tot * a0 + l1 * a1;
+  }
   if (!row_ok) return;
-  const float l_tot = l_run + half_swap(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   float* orow = p.part_o + ((size_t)split * p.rows_total + grow) * D;
 #pragma unroll
@@ -873,13 +942,13 @@ DecodePlan plan_decode(const DecodeArgs& a, uint64_t max_workspace_bytes) {
   DecodePlan pl;
   const int64_t keys = (int64_t)a.Lc + (a.append ? a.n_new : 0);
   const int64_t R = (int64_t)(a.n_q / a.n_kv) * a.n_new;
-  // a GQA group of at least four 32-row blocks shares each K/V block among
-  // the 8 waves of a workgroup (one workgroup per CU: its registers), else
-  // one wave per workgroup (kWgPerCu per CU: their LDS)
+  // A GQA group of at least four 32-row blocks shares each K/V tile among the 8
+  // waves of a workgroup (one workgroup per CU: its registers), else one wave
+  // per 32-row block (kWgPerCu per CU: their LDS).
   pl.waves = R >= 4 * kRows ? 8 : 1;
   const int64_t bk = pl.waves == 8 ? kPingPongKB * kKeys : kKeys;
   const int64_t nblk = (keys + bk - 1) / bk;
-  const int64_t n_rb = (R + kRows * pl.waves - 1) / (kRows * pl.waves);
+  int64_t n_rb = (R + kRows * pl.waves - 1) / (kRows * pl.waves);
   // one round of workgroups, at least two key blocks each
   const int64_t target = pl.waves == 1 ? 256 * kWgPerCu : 256;
   int64_t n_split = target / (a.n_kv * n_rb);
@@ -887,6 +956,16 @@ DecodePlan plan_decode(const DecodeArgs& a, uint64_t max_workspace_bytes) {
   if (n_split < 1) n_split = 1;
   int64_t bps = nblk > 0 ? (nblk + n_split - 1) / n_split : 0;
   if (bps > 0) n_split = (nblk + bps - 1) / bps;
+  // Three or four row blocks: the same splits, but two groups of four waves per
+  // workgroup in place of a workgroup per row block, each reading the keys
+  // again (85 rows x 30001 keys x 8 heads of d = 128: 40.7 -> 31.7 us; 124 rows
+  // x 16384: 30.9 -> 25.6).  Splits of fewer than four blocks are too short for
+  // the groups' merge (124 rows x 1000: 13.5 -> 14.7 us).  With two row blocks
+  // the second read comes from cache and the groups gain nothing.
+  if (pl.waves == 1 && n_rb > 2 && bps >= 4) {
+    pl.waves = 4;
+    n_rb = 1;
+  }
   // a workspace limit caps the splits (longer splits, the same kernels)
   const int64_t rows_total = (int64_t)a.n_q * a.n_new;
   // per (split, row): fp32 O and LSE, or fp16 O, its scale and the LSE
@@ -941,6 +1020,18 @@ hipError_t decode_scratch(void** ptr) {
   return hipSuccess;
 }
 
+template <int D>
+static void launch_partials(const DecParams& p, int waves, dim3 grid, hipStream_t stream) {
+  switch (waves) {
+    case 8: hipLaunchKernelGGL((decode_pingpong_kernel<D>), grid, dim3(512), 0, stream, p); break;
+    case 4:
+      hipLaunchKernelGGL((decode_partial_kernel<D, 4, 2, kGroupRing>), grid, dim3(512), 0, stream, p);
+      break;
+    default:
+      hipLaunchKernelGGL((decode_partial_kernel<D, 1, 1, kRing>), grid, dim3(64), 0, stream, p);
+  }
+}
+
 hipError_t launch_decode(const DecodeArgs& a, const DecodePlan& pl, hipStream_t stream) {
   DecParams p;
   p.q = a.q; p.kc = a.kc; p.vc = a.vc; p.kn = a.kn; p.vn = a.vn;
@@ -965,14 +1056,8 @@ hipError_t launch_decode(const DecodeArgs& a, const DecodePlan& pl, hipStream_t 
   p.blocks_per_split = pl.blocks_per_split;
   p.scale_log2 = a.scale_log2;
   const dim3 grid((unsigned)pl.n_split, (unsigned)a.n_kv, (unsigned)pl.row_blocks);
-  const dim3 block((unsigned)(64 * pl.waves));
-  if (a.head_dim == 128) {
-    if (pl.waves == 8) hipLaunchKernelGGL((decode_pingpong_kernel<128>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((decode_partial_kernel<128>), grid, block, 0, stream, p);
-  } else {
-    if (pl.waves == 8) hipLaunchKernelGGL((decode_pingpong_kernel<64>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((decode_partial_kernel<64>), grid, block, 0, stream, p);
-  }
+  if (a.head_dim == 128) launch_partials<128>(p, pl.waves, grid, stream);
+  else launch_partials<64>(p, pl.waves, grid, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (pl.waves == 8)

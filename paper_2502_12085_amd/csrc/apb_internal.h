@@ -52,13 +52,13 @@ struct DecodeArgs {
 };
 
 // How a decode call splits its keys; the workspace holds one partial per
-// split and row: fp32 O and LSE (one-wave workgroups), or fp16 O with a
-// per-row power-of-two scale and the LSE (eight-wave workgroups).
+// split and row: fp32 O and LSE (one or four row blocks), or fp16 O with a
+// per-row power-of-two scale and the LSE (eight).
 struct DecodePlan {
   int n_split;
   int blocks_per_split;
   int row_blocks;      // workgroups along the rows (each waves * 32 rows)
-  int waves;           // waves per workgroup sharing one K/V ring (1 or 8)
+  int waves;           // 32-row blocks of a workgroup that share its key blocks (1, 4 or 8)
   uint64_t workspace_bytes;
 };
 

@@ -1,0 +1,42 @@
+"""GPU parity of the decoding step for 65 to 127 rows per KV head, where two
+groups of four waves share a workgroup and meet in LDS, against the fp64
+oracle at the decode test's bar: every count of row blocks and of waves
+without rows, splits whose groups own unequal numbers of key blocks (one, and
+none for the second group, in the last split), masked new tokens, both head
+sizes, and the running max moving late (softmax scale 1.0) by other amounts in
+the two groups."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2502_12085_amd import inputs
+from gpu_util import O_REL_PEAKED, assert_attention_close, need_gpu, say
+from test_gpu_decode import _run_decode
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape, scale", [
+    # n_q, n_kv, d, Lc, n_new, append
+    ((32, 16, 64, 2100, 33, 1), 0.0),    # 66 rows: the third row block has two
+    ((48, 16, 128, 2500, 25, 0), 0.0),   # 75 rows, 79 blocks in splits of 5
+    ((64, 16, 128, 2049, 31, 1), 0.0),   # 124 rows: four row blocks
+    ((40, 8, 128, 4500, 17, 1), 0.0),    # 85 rows, GQA 5
+    ((14, 2, 64, 15380, 18, 0), 0.0),    # 126 rows, two heads, last split of one block
+    ((127, 127, 64, 200, 100, 1), 0.0),  # one split per head, new tokens longer than a block
+    ((32, 16, 128, 2100, 33, 1), 1.0),
+    ((8, 2, 64, 15990, 31, 1), 1.0),
+])
+def test_decode_wave_groups(shape, scale):
+    need_gpu()
+    n_q, n_kv, d, lc, n_new, app = shape
+    say(f"[decode groups] {shape} scale {scale}")
+    case = inputs.make_decode_case(n_q, n_kv, d, [lc], n_new, seed=23)
+    kc, vc = case["caches"][0]
+    kn = case["k_new"] if app else None
+    vn = case["v_new"] if app else None
+    o, lse = _run_decode(case["q"], kc, vc, kn, vn, n_q, n_kv, d, scale)
+    kw = dict(scale=scale) if scale else {}
+    o_ref, lse_ref = oracle.decode_attention_ref(case["q"], kc, vc, kn, vn, **kw)
+    assert_attention_close(o, lse, o_ref, lse_ref, f"decode groups {shape}",
+                           **(dict(o_rel=O_REL_PEAKED) if scale else {}))
