@@ -47,6 +47,8 @@ class Problem(ctypes.Structure):
     @classmethod
     def of(cls, p) -> "Problem":
         """From any object with the same field names (e.g. inputs.Problem)."""
+        if isinstance(p, cls):
+            return p
         return cls(*(int(getattr(p, f)) for f, _ in cls._fields_))
 
 
@@ -158,23 +160,31 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+# What a call costs the host counts: a small decoding step's kernels take 9 us
+# and its launches 5.  The current stream's handle comes from the raw lookup
+# (0.5 us with the device's index; a torch.cuda.Stream object took 3), and a
+# tensor's checks are one expression: 11.7 -> 9.4 us per decode_attention call,
+# 7.9 -> 5.6 per merge_partials call.
 def _ptr(t, name, dtypes):
     """Device pointer of a contiguous CUDA/HIP tensor, or None."""
     if t is None:
         return None
+    if t.is_cuda and t.dtype in dtypes and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if t.dtype not in dtypes:
         raise ValueError(f"{name} has dtype {t.dtype}, expected one of {dtypes}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return t.data_ptr()
+    raise ValueError(f"{name} must be contiguous")
 
 
 def _stream(stream):
-    import torch
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            return torch.cuda.current_stream().cuda_stream
+        return raw(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
