@@ -48,6 +48,9 @@
 //    the max pass and the O rescale are off the common path.
 //  * Tiles crossing a row's visible end are masked element-wise; tiles past
 //    every row of the workgroup are not visited.
+//  * Problems of few query tiles take a key-split form of the same kernel: both
+//    groups own the same 128 rows and every second key tile each, and merge in
+//    LDS.
 //  * Grid order puts the query tiles with the longest key prefix first, and
 //    keeps a GQA group's workgroups on one XCD (one L2) when n_kv % 8 == 0.
 #include <math.h>
@@ -72,8 +75,7 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kRowsPerWave = 32;
 constexpr int kBM = kRowsPerWave * kWaves;  // query rows per workgroup
 constexpr int kBN = 128;                           // keys per tile
-constexpr int kKB = kBN / 16;                      // 16-key MFMA blocks per tile
-constexpr int kNPC = kBN / 32;                     // 32-key chunks per tile (PV k-steps)
+constexpr int kSplitBM = kRowsPerWave * kGroupWaves;  // the same of the key-split form
 constexpr int kStages = 2;                         // LDS ring depth for K and V tiles
 constexpr int kPD = 2;                             // LDS operand read-ahead (MFMA steps)
 constexpr int kXcds = 8;                    // MI355X: 8 XCDs, workgroups dealt round-robin
@@ -168,9 +170,18 @@ __device__ __forceinline__ void phase_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int D>
+// SPLIT: the key-split form for problems with few query tiles.  The two groups
+// own the same 128 rows and every second key tile each (group g the tiles 2t +
+// g, 64 keys at d = 128 so that both groups' rings fit), copy their own K and V,
+// and meet in LDS at the end: twice the workgroups, half the tiles in a row.
+template <int D, bool SPLIT>
 __global__ void __launch_bounds__(kThreads, 1)
 attn_fwd_kernel(Params p) {
+  constexpr int BM = SPLIT ? kSplitBM : kBM;     // query rows per workgroup
+  constexpr int kBN = SPLIT ? 8192 / D : apb::kBN;  // keys per tile
+  constexpr int kKB = kBN / 16;                  // 16-key MFMA blocks per tile
+  constexpr int kNPC = kBN / 32;                 // 32-key chunks per tile (PV k-steps)
+  constexpr int RINGS = SPLIT ? 2 : 1;           // K and V rings (one per group)
   constexpr int PIECE_ELEMS = 512;               // one 1 KiB DMA piece, in bf16
   constexpr int ROWS_PER_PIECE = PIECE_ELEMS / D;
   constexpr int PIECES = kBN * D / PIECE_ELEMS;  // pieces per tile per tensor
@@ -188,8 +199,8 @@ attn_fwd_kernel(Params p) {
 
   // 256-byte aligned: operand addresses XOR step bits into the low byte of
   // a stage base plus lane offset
-  __shared__ __attribute__((aligned(256))) uint16_t k_lds[kStages][kBN * D];
-  __shared__ __attribute__((aligned(256))) uint16_t v_lds[kStages][kBN * D];
+  __shared__ __attribute__((aligned(256))) uint16_t k_lds[RINGS * kStages][kBN * D];
+  __shared__ __attribute__((aligned(256))) uint16_t v_lds[RINGS * kStages][kBN * D];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -202,9 +213,14 @@ attn_fwd_kernel(Params p) {
   int head, qtile;
   map_block(p, blockIdx.x, head, qtile);
   const int kvh = head / p.group;
-  const int r0 = qtile * kBM;
-  const int r_last = min(r0 + kBM, p.M) - 1;
-  const int ntiles = (vis_end(r_last, p.La, p.Lp) + kBN - 1) / kBN;
+  const int r0 = qtile * BM;
+  const int r_last = min(r0 + BM, p.M) - 1;
+  // tiles of a group (SPLIT: of the longer one; the other's last may lie past
+  // the last key and is masked)
+  const int ntiles = ((vis_end(r_last, p.La, p.Lp) + kBN - 1) / kBN + RINGS - 1) / RINGS;
+  const int ring = SPLIT ? kStages * grp : 0;
+  // first concatenated key of this wave's tile t
+  auto tile_key = [&](int t) __attribute__((always_inline)) { return (SPLIT ? 2 * t + grp : t) * kBN; };
 
   // Schedule, in phases separated by workgroup barriers.  Group A runs the
   // MFMA step of tile t, {S(t) = K(t) Q^T, O += P(t-1) V(t-1)}, in phase 2t
@@ -220,6 +236,10 @@ attn_fwd_kernel(Params p) {
   //    2T+1 (its softmax phase).
   // The barrier after each wait makes the tile visible to the phase that
   // first reads it.
+  // SPLIT: either group copies K(t+2) and V(t+1) at the start of its softmax of
+  // S(t), when its MFMA step t has read K(t) and V(t-1) from those stages, and
+  // waits for the copies of its softmax of S(t-1) at the end of it: K(t+1) and
+  // V(t), which its next MFMA step reads.
 
   // Copy lanes: global_load_lds_dwordx4 puts lane l's 16 bytes at M0 +
   // inst_offset + 16*l and reads them from saddr + voffset + inst_offset, so
@@ -294,10 +314,87 @@ attn_fwd_kernel(Params p) {
       }
     }
   };
+  // SPLIT: this group's K (which = 0) or V (1) tile t, WP copies per wave; a
+  // cursor per tensor (the V copies run a tile behind)
+  int sp_end[2] = {0, 0};
+  uint64_t sp_base[2] = {0, 0};
+  // end and base of the segment that holds concatenated row c
+  auto segment = [&](int which, int c, int& end, uint64_t& base) __attribute__((always_inline)) {
+    const uint64_t loc = (uint64_t)(which ? p.v : p.k), pass = (uint64_t)(which ? p.vp : p.kp);
+    if (c < p.La) {
+      end = p.La;
+      base = loc + (uint64_t)(2 * D) * ((uint64_t)kvh * p.M);
+    } else if (c < p.La + p.Lp) {
+      const int sl = (c - p.La) / p.lp;
+      end = p.La + (sl + 1) * p.lp;
+      base = pass + (uint64_t)(2 * D) * (uint64_t)((int64_t)(sl * p.n_kv + kvh) * p.lp -
+                                                   (p.La + (int64_t)sl * p.lp));
+    } else {
+      end = p.Ktot;
+      base = loc + (uint64_t)(2 * D) * (uint64_t)((int64_t)kvh * p.M - p.Lp);
+    }
+  };
+  // Per-lane source offset of piece 0; piece j's, less its j KiB, follows from
+  // it: a piece is 512 / D rows, so V's swizzle (row mod 4) and K's at d = 64
+  // (row mod 8) are the same in every piece, and K's at d = 128 (row mod 16)
+  // differs by 4j, which is 64j bytes.
+  const int sp_row = wig * WP * ROWS_PER_PIECE + lane / KCH;
+  const uint32_t sp_k = 2u * (uint32_t)(sp_row * D + 8 * (lane % KCH ^ k_swz<D>(lane / KCH)));
+  const uint32_t sp_v = 2u * (uint32_t)(sp_row * D + 8 * (lane % KCH ^ v_swz<D>(lane / KCH)));
+  auto sp_off = [&](int which, int j) __attribute__((always_inline)) -> uint32_t {
+    return which ? sp_v : D == 128 ? sp_k ^ (64u * (uint32_t)j) : sp_k;
+  };
+  auto issue_own = [&](int t, int which) __attribute__((always_inline)) {
+    const int c0 = tile_key(t);
+    if (c0 >= sp_end[which]) segment(which, c0, sp_end[which], sp_base[which]);
+    uint16_t* stage = which ? v_lds[ring + t % kStages] : k_lds[ring + t % kStages];
+    const uint32_t dst =
+        __builtin_amdgcn_readfirstlane(lds_offset(&stage[wig * WP * PIECE_ELEMS]));
+    if (c0 + kBN <= sp_end[which]) {
+      const uint64_t base = uniform64(sp_base[which] + (uint64_t)(2 * D) * (uint32_t)c0);
+      asm volatile(
+          "s_mov_b32 m0, %5\n\t"
+          "global_load_lds_dwordx4 %0, %4\n\t"
+          "global_load_lds_dwordx4 %1, %4 offset:1024\n\t"
+          "global_load_lds_dwordx4 %2, %4 offset:2048\n\t"
+          "global_load_lds_dwordx4 %3, %4 offset:3072" ::"v"(sp_off(which, 0)),
+          "v"(sp_off(which, 1)), "v"(sp_off(which, 2)), "v"(sp_off(which, 3)), "s"(base), "s"(dst)
+          : "memory");
+    } else {
+      // The tile straddles a segment end or the last key (rows past that repeat
+      // it): rows up to the end from this segment, the others from the next, or,
+      // where that one ends inside the tile too, looked up one by one (about
+      // 1 us per tile and tensor, all told, against 0.1).
+      int end2 = sp_end[which];
+      uint64_t base2 = sp_base[which];
+      if (sp_end[which] < p.Ktot) segment(which, sp_end[which], end2, base2);
+      if (min(c0 + kBN, p.Ktot) <= end2) {
+#pragma unroll
+        for (int j = 0; j < WP; ++j) {
+          const int c = min(c0 + sp_row + j * ROWS_PER_PIECE, p.Ktot - 1);
+          const uint64_t src = (c < sp_end[which] ? sp_base[which] : base2) +
+                               (uint64_t)(2 * D) * (uint32_t)c + (sp_off(which, j) & (2 * D - 1));
+          asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src),
+                       "s"(dst + 1024u * j)
+                       : "memory");
+        }
+      } else {
+#pragma unroll 1
+        for (int j = 0; j < WP; ++j) {
+          const int c = min(c0 + sp_row + j * ROWS_PER_PIECE, p.Ktot - 1);
+          const uint16_t* src = key_row_sel<D>(p, which ? p.v : p.k, which ? p.vp : p.kp, kvh, c) +
+                                (sp_off(which, j) & (2 * D - 1)) / 2;
+          asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src),
+                       "s"(dst + 1024u * j)
+                       : "memory");
+        }
+      }
+    }
+  };
   // Every wave has at most one tile's copies in flight when it waits.
   auto land = []() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
 
-  const int w_first = r0 + kRowsPerWave * wave;
+  const int w_first = r0 + kRowsPerWave * (SPLIT ? wig : wave);
   const bool w_valid = w_first < p.M;
   const int w_lo = vis_end(w_first, p.La, p.Lp);  // shortest visible prefix in the wave
   // 16x16x32 MFMAs: lane (li, lg) is column li of a 16-wide block and holds
@@ -396,8 +493,8 @@ attn_fwd_kernel(Params p) {
   // and last tiles.  Every step is two MFMAs per stream (the two query
   // blocks share the operand read).  The scheduling barriers keep the
   // read-ahead distance.
-  auto k_stage = [&](int t) __attribute__((always_inline)) { return lds_offset(k_lds[t % kStages]) + k_lane; };
-  auto v_stage = [&](int t) __attribute__((always_inline)) { return lds_offset(v_lds[t % kStages]) + v_lane; };
+  auto k_stage = [&](int t) __attribute__((always_inline)) { return lds_offset(k_lds[ring + t % kStages]) + k_lane; };
+  auto v_stage = [&](int t) __attribute__((always_inline)) { return lds_offset(v_lds[ring + t % kStages]) + v_lane; };
   // copy_v: group A's V(t) copies, issued behind the phase's first operand
   // reads while the matrix core waits for them.
   auto qk_pv = [&](int t, bool copy_v) __attribute__((always_inline)) {
@@ -460,7 +557,7 @@ attn_fwd_kernel(Params p) {
 
   // Softmax of tile t: mask, running max, exp2, row sums, P -> bf16.
   auto softmax = [&](int t) __attribute__((always_inline)) {
-    const int c0 = t * kBN;
+    const int c0 = tile_key(t);
     if (c0 + kBN > w_lo) {  // tile crosses some row's visible end
 #pragma unroll
       for (int kb = 0; kb < kKB; ++kb)
@@ -483,7 +580,7 @@ attn_fwd_kernel(Params p) {
     // exp2, then its sums and bf16 packing), so that no instruction waits on
     // the latency of the one before it.
     float rs[2][2];
-    auto exp_tile = [&]() __attribute__((always_inline)) {
+    auto exp_tile = [&](const float (&m_ref)[2]) __attribute__((always_inline)) {
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb) rs[qb][0] = rs[qb][1] = 0.f;
 #pragma unroll
@@ -495,7 +592,7 @@ attn_fwd_kernel(Params p) {
           for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-              e[h][qb][r] = fmaf(s[2 * kc + h][qb][r], p.scale_log2, -m_run[qb]);
+              e[h][qb][r] = fmaf(s[2 * kc + h][qb][r], p.scale_log2, -m_ref[qb]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -517,7 +614,7 @@ attn_fwd_kernel(Params p) {
         }
       }
     };
-    exp_tile();
+    exp_tile(m_run);
     const float l0 = rs[0][0] + rs[0][1], l1 = rs[1][0] + rs[1][1];
     if (__any(!(l0 <= kSumLimit) || !(l1 <= kSumLimit))) {
 #pragma unroll
@@ -537,7 +634,14 @@ attn_fwd_kernel(Params p) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) oacc[db][qb][r] *= alpha;
       }
-      exp_tile();
+      if constexpr (SPLIT) {
+        // a row that sees none of the group's keys yet keeps m_run = -inf, P = 0
+        const float m_ref[2] = {m_run[0] == -INFINITY ? 0.f : m_run[0],
+                                m_run[1] == -INFINITY ? 0.f : m_run[1]};
+        exp_tile(m_ref);
+      } else {
+        exp_tile(m_run);
+      }
     }
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) l_run[qb] += rs[qb][0] + rs[qb][1];
@@ -551,7 +655,82 @@ attn_fwd_kernel(Params p) {
   auto base_prio = []() __attribute__((always_inline)) { __builtin_amdgcn_s_setprio(0); };
   // Both groups pass the same number of barriers: one after the prologue,
   // then two per tile, then two for the last PV products.
-  if (grp == 0) {
+  if constexpr (SPLIT) {
+    // each group in its own phases as below: MFMA(t), then softmax(t) with the
+    // copies of the step after next; group B starts a phase later
+    issue_own(0, 0);
+    if (1 < ntiles) issue_own(1, 0);
+    issue_own(0, 1);
+    // K(0) has landed once only K(1) and V(0) are outstanding
+    if (1 < ntiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * WP) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WP) : "memory");
+    phase_barrier();
+    if (grp == 1) phase_barrier();
+    auto softmax_turn = [&](int t) __attribute__((always_inline)) {
+      if (t + 2 < ntiles) issue_own(t + 2, 0);
+      if (t + 1 < ntiles) issue_own(t + 1, 1);
+      softmax(t);
+      if (t + 2 < ntiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * WP) : "memory");
+      else if (t + 1 < ntiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WP) : "memory");
+      else land();
+    };
+    mfma_prio();
+    qk_only(0, false);
+    base_prio();
+    phase_barrier();
+    softmax_turn(0);
+    phase_barrier();
+    for (int t = 1; t < ntiles; ++t) {
+      mfma_prio();
+      qk_pv(t, false);
+      base_prio();
+      phase_barrier();
+      softmax_turn(t);
+      phase_barrier();
+    }
+    mfma_prio();
+    pv_only(ntiles - 1);
+    base_prio();
+    phase_barrier();
+    if (grp == 0) phase_barrier();
+    // group B's O, running max and sum through LDS, whose tiles are done with
+    static_assert(NDB * 2 * 4 * 64 * kGroupWaves * 2 <= RINGS * kStages * kBN * D, "merge buffer");
+    float* const o_lds = reinterpret_cast<float*>(&k_lds[0][0]) + wig * (NDB * 2 * 4 * 64) + lane;
+    float* const m_lds = reinterpret_cast<float*>(&v_lds[0][0]) + wig * (4 * 64) + lane;
+    float l_own[2];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) l_own[qb] = row_sum(l_run[qb]);
+    if (grp == 1) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o_lds[64 * ((2 * db + qb) * 4 + r)] = oacc[db][qb][r];
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        m_lds[64 * qb] = m_run[qb];
+        m_lds[64 * (2 + qb)] = l_own[qb];
+      }
+    }
+    __syncthreads();
+    if (grp == 1) return;
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      // group A has seen key 0, so its max is finite
+      const float mb = m_lds[64 * qb], lb = m_lds[64 * (2 + qb)];
+      const float m = fmaxf(m_run[qb], mb);
+      const float wa = __builtin_amdgcn_exp2f(m_run[qb] - m);
+      const float wb = __builtin_amdgcn_exp2f(mb - m);  // mb = -inf gives 0
+      m_run[qb] = m;
+      l_run[qb] = l_own[qb] * wa + lb * wb;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          oacc[db][qb][r] = oacc[db][qb][r] * wa + o_lds[64 * ((2 * db + qb) * 4 + r)] * wb;
+    }
+  } else if (grp == 0) {
     // group A: copies V; MFMA(t) in phase 2t, softmax(t) in phase 2t+1
     phase_barrier();  // K(0) landed (copied by group B)
     mfma_prio();
@@ -608,7 +787,8 @@ attn_fwd_kernel(Params p) {
   if (!w_valid) return;
   float l_tot[2];
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) l_tot[qb] = row_sum(l_run[qb]);  // every lane takes part
+  for (int qb = 0; qb < 2; ++qb)
+    l_tot[qb] = SPLIT ? l_run[qb] : row_sum(l_run[qb]);  // every lane takes part
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     if (rq[qb] >= p.M) continue;
@@ -630,6 +810,19 @@ attn_fwd_kernel(Params p) {
 
 int attention_tile_rows() { return kBM; }
 
+// The key-split form is for problems whose 256-row workgroups make at most one
+// round: the longest of them is then a serial chain of tiles while CUs idle.
+// Past that the chip is full either way and the 256-row form does less work per
+// key (a K or V tile serves twice the rows).  Measured, 32 / 8 heads of d = 128:
+// 1024 rows and 384 passed keys 48.1 -> 28 us; 1324 rows and 381: 54.0 -> 42.4;
+// 2000 rows (256 workgroups) 55.2 -> 44.4; 2500 rows (320) 68.6 against 69.6;
+// 4096 rows 127 against 140.  d = 64, 4 / 1 heads, 8192 rows (128): 126 -> 79.
+// It needs keys for both groups: 100 rows of d = 64, one tile, 8.2 against 9.1.
+static bool use_split(const Params& p, int head_dim) {
+  const int64_t wgs = ((int64_t)p.M + kBM - 1) / kBM * p.n_q;
+  return wgs <= 256 && p.Ktot > 8192 / head_dim;
+}
+
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
   Params p;
   p.q = a.q; p.k = a.k; p.v = a.v; p.kp = a.kp; p.vp = a.vp; p.o = a.o; p.lse = a.lse;
@@ -637,14 +830,19 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
   p.M = a.La + a.Lb;
   p.Ktot = a.La + a.Lp + a.Lb;
   p.n_q = a.n_q; p.n_kv = a.n_kv; p.group = a.n_q / a.n_kv;
-  p.n_qtiles = (p.M + kBM - 1) / kBM;
   p.xcd_map = (p.n_kv % kXcds) == 0;
   p.scale_log2 = a.scale_log2;
+  const bool split = use_split(p, a.head_dim);
+  const int bm = split ? kSplitBM : kBM;
+  p.n_qtiles = (p.M + bm - 1) / bm;
   const dim3 grid((unsigned)(p.n_qtiles * p.n_q));
-  if (a.head_dim == 128)
-    hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(kThreads), 0, stream, p);
-  else
-    hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(kThreads), 0, stream, p);
+  if (a.head_dim == 128) {
+    if (split) hipLaunchKernelGGL((attn_fwd_kernel<128, true>), grid, dim3(kThreads), 0, stream, p);
+    else hipLaunchKernelGGL((attn_fwd_kernel<128, false>), grid, dim3(kThreads), 0, stream, p);
+  } else {
+    if (split) hipLaunchKernelGGL((attn_fwd_kernel<64, true>), grid, dim3(kThreads), 0, stream, p);
+    else hipLaunchKernelGGL((attn_fwd_kernel<64, false>), grid, dim3(kThreads), 0, stream, p);
+  }
   return hipGetLastError();
 }
 
