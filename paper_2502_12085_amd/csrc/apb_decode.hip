@@ -60,6 +60,14 @@ constexpr int kKeys = 32;   // keys per MFMA block (the MFMA M side)
 constexpr int kWgPerCu = 3; // one-wave workgroups per CU (LDS: 3 x 48 KiB at d = 128)
 constexpr int kRing = 3;    // LDS stages of K and V blocks per one-wave workgroup
 constexpr int kGroupRing = 4;  // LDS stages of each of the two groups of a four-wave workgroup
+// The one-launch form, for few keys: that many one-wave groups per workgroup
+// (two stages each in 128 KiB of LDS), at most that many key blocks.  The step is
+// then launches and latency: against split and merge, 32 / 8 heads of d = 128,
+// one token: 100 keys 9.7 -> 6.9 us, 250 9.8 -> 8.0, 500 (16 blocks) 9.8 against
+// 9.6, 750 9.7 against 11.1; 4 / 1 heads of d = 64: 500 keys 9.6 -> 6.6, 1000 (32
+// blocks) 9.7 -> 7.9, 2000 9.7 against 10.5.
+constexpr int one_launch_groups(int d) { return d == 128 ? 4 : 8; }
+constexpr int one_launch_blocks(int d) { return d == 128 ? 12 : 32; }
 constexpr float kSumLimit = 8192.f;  // lazy rescale: largest block row-half sum against a stale max
 
 struct DecParams {
@@ -140,9 +148,10 @@ constexpr int kPingPongKB = 4;
 // wave w of a group owns the 32-row block w, and a group's waves share its
 // copies, two copying K and two V (a wave without rows only copies).  One barrier
 // per block orders copies and reads; the groups' results meet in LDS, so that a
-// split is one partial.
+// split is one partial.  W = 1 with KS groups is the one-launch form: one split,
+// whose partial is the result.
 template <int D, int W, int KS, int RING>
-__global__ void __launch_bounds__(64 * W * KS, KS) decode_partial_kernel(DecParams p) {
+__global__ void __launch_bounds__(64 * W * KS, (W * KS + 3) / 4) decode_partial_kernel(DecParams p) {
   constexpr int BK = kKeys;                  // keys per ring block
   constexpr int NKC = D / 16;                // MFMA k-steps over head_dim
   constexpr int NDB = D / 32;                // 32-dim blocks of O^T
@@ -157,7 +166,7 @@ __global__ void __launch_bounds__(64 * W * KS, KS) decode_partial_kernel(DecPara
   __shared__ __attribute__((aligned(256))) uint16_t v_lds[KS * RING][BK * D];
 
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
-  const int wave_id = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_id = W * KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wave = wave_id % W, grp = wave_id / W;
   const int split = blockIdx.x, kvh = blockIdx.y, rb = blockIdx.z * W + wave;
   const int Ltot = p.Lc + (p.append ? p.n_new : 0);
@@ -304,7 +313,9 @@ __global__ void __launch_bounds__(64 * W * KS, KS) decode_partial_kernel(DecPara
     // the block RING-1 turns on reuses the last turn's stage, whose reads are done
     if (b + (RING - 1) * KS < b1) load_block(b + (RING - 1) * KS, grp * RING + (i + RING - 1) % RING);
     if constexpr (W > 1)
-      if (!has_rows || b >= b1) continue;
+      if (!has_rows) continue;
+    if constexpr (KS > 1)
+      if (b >= b1) continue;
     // The operand reads of each product are issued together ahead of its
     // MFMAs (the scheduling barriers stop the compiler from re-serialising
     // read, wait, MFMA): the K operands, the QK MFMAs, the V operands (read
@@ -406,33 +417,36 @@ __global__ void __launch_bounds__(64 * W * KS, KS) decode_partial_kernel(DecPara
 
   float l_tot = l_run + half_swap(l_run);
   if constexpr (KS > 1) {
-    // the second group's O, running max and sum through LDS (the rings are done
-    // with), rescaled to the larger max of the two
-    static_assert(KS == 2 && NDB * 16 * 64 * W * 2 <= KS * RING * BK * D, "merge buffer");
-    float* const o_lds = reinterpret_cast<float*>(&k_lds[0][0]) + wave * (NDB * 16 * 64) + lane;
+    // the other groups' O, running max and sum through LDS (the rings are done
+    // with), rescaled to the larger max one after another
+    constexpr int OUT = NDB * 16 * 64;  // floats of a wave's O
+    static_assert(OUT * W * (KS - 1) * 2 <= KS * RING * BK * D, "merge buffer");
+    float* const o_lds = reinterpret_cast<float*>(&k_lds[0][0]) + wave * OUT + lane;
     float* const m_lds = reinterpret_cast<float*>(&v_lds[0][0]) + wave * 128 + lane;
     asm volatile("s_barrier" ::: "memory");
-    if (grp == 1) {
+    if (grp > 0) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o_lds[64 * (16 * db + r)] = oacc[db][r];
-      m_lds[0] = m_run;
-      m_lds[64] = l_tot;
+        for (int r = 0; r < 16; ++r) o_lds[(grp - 1) * W * OUT + 64 * (16 * db + r)] = oacc[db][r];
+      m_lds[(grp - 1) * W * 128] = m_run;
+      m_lds[(grp - 1) * W * 128 + 64] = l_tot;
     }
     __syncthreads();
-    if (grp == 1) return;
-    const float m1 = m_lds[0], l1 = m_lds[64];
-    const float m = fmaxf(m_run, m1);
-    const float a0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
-    const float a1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
+    if (grp > 0) return;
+    for (int g = 0; g < KS - 1; ++g) {
+      const float m1 = m_lds[g * W * 128], l1 = m_lds[g * W * 128 + 64];
+      const float m = fmaxf(m_run, m1);
+      const float a0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
+      const float a1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+      for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        oacc[db][r] = oacc[db][r] * a0 + o_lds[64 * (16 * db + r)] * a1;
-    m_run = m;
-    l_tot = l_tot * a0 + l1 * a1;
+        for (int r = 0; r < 16; ++r)
+          oacc[db][r] = oacc[db][r] * a0 + o_lds[g * W * OUT + 64 * (16 * db + r)] * a1;
+      m_run = m;
+      l_tot = l_tot * a0 + l1 * a1;
+    }
   }
   if (!row_ok) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -975,6 +989,7 @@ DecodePlan plan_decode(const DecodeArgs& a, uint64_t max_workspace_bytes) {
     const int64_t cap = (int64_t)(max_workspace_bytes / per_split);
     if (cap < 1) {
       pl.n_split = 0;  // does not fit
+      pl.one_launch = false;
       pl.blocks_per_split = 0;
       pl.row_blocks = (int)n_rb;
       pl.workspace_bytes = per_split;
@@ -983,10 +998,17 @@ DecodePlan plan_decode(const DecodeArgs& a, uint64_t max_workspace_bytes) {
     bps = (nblk + cap - 1) / cap;
     n_split = (nblk + bps - 1) / bps;
   }
+  pl.workspace_bytes = (uint64_t)n_split * per_split;
+  pl.one_launch = false;
+  // (the workspace keeps the size of the splits)
+  if (pl.waves == 1 && n_split > 1 && nblk <= one_launch_blocks(a.head_dim)) {
+    pl.one_launch = true;
+    n_split = 1;
+    bps = nblk;
+  }
   pl.n_split = (int)n_split;
   pl.blocks_per_split = (int)bps;
   pl.row_blocks = (int)n_rb;
-  pl.workspace_bytes = (uint64_t)n_split * per_split;
   return pl;
 }
 
@@ -1021,8 +1043,13 @@ hipError_t decode_scratch(void** ptr) {
 }
 
 template <int D>
-static void launch_partials(const DecParams& p, int waves, dim3 grid, hipStream_t stream) {
-  switch (waves) {
+static void launch_partials(const DecParams& p, const DecodePlan& pl, dim3 grid, hipStream_t stream) {
+  constexpr int G = one_launch_groups(D);
+  if (pl.one_launch) {
+    hipLaunchKernelGGL((decode_partial_kernel<D, 1, G, 2>), grid, dim3(64 * G), 0, stream, p);
+    return;
+  }
+  switch (pl.waves) {
     case 8: hipLaunchKernelGGL((decode_pingpong_kernel<D>), grid, dim3(512), 0, stream, p); break;
     case 4:
       hipLaunchKernelGGL((decode_partial_kernel<D, 4, 2, kGroupRing>), grid, dim3(512), 0, stream, p);
@@ -1044,11 +1071,12 @@ hipError_t launch_decode(const DecodeArgs& a, const DecodePlan& pl, hipStream_t 
     p.part_scale = reinterpret_cast<float*>(p.part_h + parts * a.head_dim);
     p.part_lse = p.part_scale + parts;
   } else {
-    // fp32 O, then the LSEs
-    p.part_o = a.workspace;
+    // fp32 O, then the LSEs; the partial of one split is the result itself
+    const bool whole = pl.n_split == 1;
+    p.part_o = whole ? a.o : a.workspace;
     p.part_h = nullptr;
     p.part_scale = nullptr;
-    p.part_lse = a.workspace + parts * a.head_dim;
+    p.part_lse = whole ? a.lse : a.workspace + parts * a.head_dim;
   }
   p.Lc = a.Lc; p.n_new = a.n_new; p.append = a.append; p.n_kv = a.n_kv;
   p.R = (a.n_q / a.n_kv) * a.n_new;
@@ -1056,10 +1084,11 @@ hipError_t launch_decode(const DecodeArgs& a, const DecodePlan& pl, hipStream_t 
   p.blocks_per_split = pl.blocks_per_split;
   p.scale_log2 = a.scale_log2;
   const dim3 grid((unsigned)pl.n_split, (unsigned)a.n_kv, (unsigned)pl.row_blocks);
-  if (a.head_dim == 128) launch_partials<128>(p, pl.waves, grid, stream);
-  else launch_partials<64>(p, pl.waves, grid, stream);
+  if (a.head_dim == 128) launch_partials<128>(p, pl, grid, stream);
+  else launch_partials<64>(p, pl, grid, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (pl.waves != 8 && pl.n_split == 1) return hipSuccess;
   if (pl.waves == 8)
     return launch_merge_t(pl.n_split, (int)rows_total, a.head_dim,
                           static_cast<const uint16_t*>(p.part_h), p.part_scale, p.part_lse,

@@ -59,6 +59,7 @@ struct DecodePlan {
   int blocks_per_split;
   int row_blocks;      // workgroups along the rows (each waves * 32 rows)
   int waves;           // 32-row blocks of a workgroup that share its key blocks (1, 4 or 8)
+  bool one_launch;     // few keys: one split, its key blocks shared among a workgroup's waves
   uint64_t workspace_bytes;
 };
 

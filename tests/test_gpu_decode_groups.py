@@ -16,7 +16,23 @@ from test_gpu_decode import _run_decode
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape, scale", [
+ONE_LAUNCH = [
+    ((8, 2, 128, 127, 1, 1), 0.0),       # four blocks, one per group
+    ((8, 2, 128, 150, 3, 0), 0.0),       # five: the second turn is one group's
+    ((32, 8, 128, 383, 1, 1), 0.0),      # 12 blocks
+    ((32, 8, 128, 384, 1, 1), 0.0),      # 13: split and merge
+    ((4, 1, 64, 97, 2, 1), 0.0),         # four blocks, four groups without any
+    ((4, 1, 64, 1022, 2, 1), 0.0),       # 32 blocks
+    ((4, 1, 64, 1023, 2, 1), 0.0),       # 33: split and merge
+    ((10, 2, 64, 700, 10, 1), 0.0),      # 50 rows: two row blocks
+    ((24, 2, 128, 200, 10, 0), 0.0),     # 120 rows in four row blocks
+    ((8, 2, 128, 40, 1, 1), 0.0),        # two blocks: one split of one group
+    ((8, 2, 128, 350, 2, 1), 1.0),
+    ((4, 1, 64, 900, 3, 1), 1.0),
+]
+
+
+@pytest.mark.parametrize("shape, scale", ONE_LAUNCH + [
     # n_q, n_kv, d, Lc, n_new, append
     ((32, 16, 64, 2100, 33, 1), 0.0),    # 66 rows: the third row block has two
     ((48, 16, 128, 2500, 25, 0), 0.0),   # 75 rows, 79 blocks in splits of 5
@@ -40,3 +56,11 @@ def test_decode_wave_groups(shape, scale):
     o_ref, lse_ref = oracle.decode_attention_ref(case["q"], kc, vc, kn, vn, **kw)
     assert_attention_close(o, lse, o_ref, lse_ref, f"decode groups {shape}",
                            **(dict(o_rel=O_REL_PEAKED) if scale else {}))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_without_keys(d):
+    q = inputs.make_decode_case(4, 2, d, [1], 3, seed=1)["q"]
+    empty = np.zeros((2, 0, d), np.uint16)
+    o, lse = _run_decode(q, empty, empty, None, None, 4, 2, d)
+    assert (o == 0).all() and np.isneginf(lse).all()
