@@ -50,29 +50,64 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const uint16_t* __restrict
 
 // RoPE in place on head-major Q [n_q][T][dh] and K [n_kv][T][dh]: the pair
 // (j, j + dh/2) of every head rotated by pos[t] * theta^(-2j/dh).  The angle
-// and its cosine and sine are computed in fp64 (positions reach 10^5 and
-// beyond, where an fp32 angle would lose its fraction), the rotation in fp32.
-// One thread per (token, j); it walks all heads with one cos/sin pair.
+// and its cosine and sine are computed in fp64 (positions reach 10^5, where an
+// fp32 angle would lose its fraction), the rotation in fp32.  A workgroup takes
+// 512 / dh rows: each thread the cosine and sine of one (row, j), into LDS, then
+// four pairs of a row and head at a time, four such quads in flight.  10240 rows
+// of Llama-3.1-8B, 210 MB: 44.8 -> 36.4 us against one pair per thread walking
+// all heads; 1256 rows, bound by latency, 17.7 -> 11.8.
 __global__ void __launch_bounds__(256) rope_kernel(uint16_t* __restrict__ q,
                                                    uint16_t* __restrict__ k,
                                                    const int32_t* __restrict__ pos, int T,
                                                    int n_q, int n_kv, int dh, double log_theta) {
-  const int half = dh / 2;
-  const int rows_per_block = 256 / half;
-  const int t = blockIdx.x * rows_per_block + threadIdx.x / half;
-  const int j = threadIdx.x % half;
-  if (t >= T) return;
-  const double ang = (double)pos[t] * exp(-2.0 * j / dh * log_theta);
-  const float c = (float)cos(ang), s = (float)sin(ang);
-  for (int hd = 0; hd < n_q + n_kv; ++hd) {
-    uint16_t* base = hd < n_q ? q + ((size_t)hd * T + t) * dh : k + ((size_t)(hd - n_q) * T + t) * dh;
-    __bf16* x = reinterpret_cast<__bf16*>(base);
-    const float lo = (float)x[j], hi = (float)x[j + half];
-    x[j] = (__bf16)(lo * c - hi * s);
-    x[j + half] = (__bf16)(hi * c + lo * s);
+  __shared__ __attribute__((aligned(16))) float cs[256], sn[256];  // [row][j]
+  const int half = dh / 2, quad_shift = dh == 128 ? 4 : 3;  // dh / 8 quads per row
+  const int rows = 256 / half, row0 = blockIdx.x * rows;
+  {
+    const int t = min(row0 + (int)threadIdx.x / half, T - 1), j = threadIdx.x % half;
+    const double ang = (double)pos[t] * exp(-2.0 * j / dh * log_theta);
+    double s64, c64;
+    sincos(ang, &s64, &c64);
+    cs[threadIdx.x] = (float)c64;
+    sn[threadIdx.x] = (float)s64;
+  }
+  __syncthreads();
+  const int n_rows = min(rows, T - row0);
+  const int items = (n_q + n_kv) * 64;  // (head, row, quad): 64 quads in a head's rows
+  constexpr int U = 4;
+  for (int i0 = threadIdx.x; i0 < items; i0 += U * 256) {
+    bf16x4 lo[U], hi[U];
+    uint16_t* at[U];
+    int cj[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * 256, hd = i >> 6, r = (i & 63) >> quad_shift;
+      const int qd = i & ((1 << quad_shift) - 1);
+      at[u] = nullptr;
+      if (i < items && r < n_rows) {
+        at[u] = (hd < n_q ? q + ((size_t)hd * T + row0 + r) * dh
+                          : k + ((size_t)(hd - n_q) * T + row0 + r) * dh) + 4 * qd;
+        cj[u] = r * half + 4 * qd;
+        lo[u] = *reinterpret_cast<const bf16x4*>(at[u]);
+        hi[u] = *reinterpret_cast<const bf16x4*>(at[u] + half);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!at[u]) continue;
+      bf16x4 a, b;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float c = cs[cj[u] + e], s = sn[cj[u] + e];
+        const float x = (float)lo[u][e], y = (float)hi[u][e];
+        a[e] = (__bf16)(x * c - y * s);
+        b[e] = (__bf16)(y * c + x * s);
+      }
+      *reinterpret_cast<bf16x4*>(at[u]) = a;
+      *reinterpret_cast<bf16x4*>(at[u] + half) = b;
+    }
   }
 }
-
 
 // Workspace carve-up (256-byte aligned pieces).
 struct LayerPlan {
