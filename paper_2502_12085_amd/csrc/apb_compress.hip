@@ -420,7 +420,10 @@ topk_gather_long_kernel(const float* __restrict__ scores, const uint16_t* __rest
       n_gt += (uint32_t)__popcll(above_m);
       const uint32_t at = __builtin_amdgcn_mbcnt_hi(
           (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, kept));
-      if ((m >> lane & 1) && at < (uint32_t)kLongCap)
+      // (m as the lanes' condition: testing m >> lane & 1 took three vector
+      // instructions more per 64 keys; 131072 power-law scores, inputs rotating,
+      // 75.9 -> 74.0 us)
+      if (__builtin_amdgcn_inverse_ballot_w64(m) && at < (uint32_t)kLongCap)
         sh.cand[wave][at] = u32x2{__float_as_uint(f[j]), chunk};
       kept += (uint32_t)__popcll(m);
     }
