@@ -36,6 +36,11 @@
 //    nothing (the CU's copy rate is the limit, not latency).  The whole layer
 //    at 1256 tokens: 1079 -> 666 us; the retaining head of 8192 tokens:
 //    151 -> 88 us.
+// Every tile width adds K in the same order, so a token's result depends on
+// neither its tile nor the number of tokens: the compressor's tie rule relies
+// on equal tokens scoring alike, bit for bit.  (Starting the K loop of each XCD
+// an eighth further on, which spreads the XCDs' fetches of weights that are not
+// in cache, would take 1000 tokens x 1024 units from 78 to 58 us.)
 // The token operand is read row-major [t][k], head-major [k / dh][t][dh]
 // (the attention output, whose heads are the O projection's K dimension), or
 // from the head-major Q, K and V tensors as one [Q heads; K heads; V heads]
@@ -152,11 +157,6 @@ gemm_kernel(GemmParams p) {
   const int t0 = p.t_begin + ttile * BT;
   const int f0 = ftile * (WM == kWGateUp ? kBF / 2 : kBF);
   const int nk = p.K / kBK;
-  // With at most 4 feature tiles (the retaining head) every XCD reads the same
-  // weights: each starts its K loop an eighth further on, so that they do not
-  // all fetch one K slab from HBM at a time (weights not in cache, 1000 tokens
-  // x 1024 units: 77 -> 58 us; more feature tiles: no gain).
-  const int k_first = SPLIT && p.nfy <= 4 ? xcd * nk / 8 : 0;
 
   // ---- copies: piece j (8 rows x 128 bytes) of each slab; wave w copies
   // weight pieces 8w .. 8w+7 and token pieces NB*w .. NB*w + NB-1.  Lane l
@@ -194,8 +194,7 @@ gemm_kernel(GemmParams p) {
   const uint16_t* const x_first = p.x + (size_t)t0 * x_ld;
   // copy q (0..CPS-1) of step kk into stage st: q < 8 weight pieces, else token pieces
   auto copy = [&](int kk, int st, int q) __attribute__((always_inline)) {
-    const int kr = kk + k_first < nk ? kk + k_first : kk + k_first - nk;
-    const int k0 = kr * kBK;
+    const int k0 = kk * kBK;
     if (q < kPieces) {
       const int i = q, j = kPieces * wave + i;
       // gate/up: rows 64..127 of either 128-row half are up-projection rows

@@ -5,7 +5,8 @@ those of the scorer and layer tests, where they are derived."""
 import numpy as np
 import pytest
 
-from gpu_util import host_bf16_to_f64, say
+from paper_2502_12085_amd import inputs
+from gpu_util import dev_bf16, host_bf16_to_f64, need_gpu, say
 from test_gpu_layer import _check_selection, _close, _oracle, _run_layer, _tiny_variant
 from test_gpu_scorer import SCORE_MAX_ABS, _run
 
@@ -47,3 +48,31 @@ def test_layer_tile_widths(rows):
     _close(host_bf16_to_f64(got["k"]), ref["k"], "K cache (post-RoPE)")
     _close(host_bf16_to_f64(got["v"]), ref["v"], "V cache")
     _check_selection(lw, inp, got, ref)
+
+
+@pytest.mark.parametrize("d, lb, hidden", [
+    (64, 200, 1024),     # 64-token tiles, the last of 8 tokens
+    (128, 5000, 1024),   # 96
+    (64, 8192, 1024),    # 128
+    (64, 17001, 1024),   # 256, then 64
+    (128, 9000, 256),    # 64 in one feature tile
+])
+def test_equal_tokens_score_alike(d, lb, hidden):
+    # every local row holds the same token: the compressor's tie rule takes the
+    # lower index of equal scores, so a token's sums may not depend on its tile
+    say(f"[tile widths] one token {lb} times, hidden {hidden}")
+    one, _, _ = _run(1, 1, d, 0, 1, hidden)
+    torch = need_gpu()
+    from paper_2502_12085_amd import apb
+    rng = np.random.default_rng(0)
+    q, k, v = (dev_bf16(inputs.f32_to_bf16_bits(rng.standard_normal((1, 1, d)).astype(np.float32)))
+               .expand(1, lb, d).contiguous() for _ in range(3))
+    w = inputs.make_scorer_weights(1, 1, d, hidden, 0)
+    f = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    p = apb.ScorerProblem(0, lb, 1, 1, d, hidden)
+    ws = torch.empty(apb.scorer_workspace_size(p), dtype=torch.uint8, device="cuda")
+    s = torch.full((1, lb), float("nan"), dtype=torch.float32, device="cuda")
+    apb.retaining_scores(p, q, k, v, dev_bf16(w["w1"]), f(w["b1"]), f(w["w2"]), f(w["b2"]), s, ws)
+    got = s.cpu().numpy().astype(np.float64)
+    say(f"  distinct scores {np.unique(got).size}, spread {got.max() - got.min():.1e}")
+    assert (got == one[0, 0]).all()  # and the score it has alone
