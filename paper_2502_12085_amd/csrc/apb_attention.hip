@@ -216,8 +216,10 @@ attn_fwd_kernel(Params p) {
   const int r0 = qtile * BM;
   const int r_last = min(r0 + BM, p.M) - 1;
   // tiles of a group (SPLIT: of the longer one; the other's last may lie past
-  // the last key and is masked)
-  const int ntiles = ((vis_end(r_last, p.La, p.Lp) + kBN - 1) / kBN + RINGS - 1) / RINGS;
+  // the last key that a row sees: it is masked and stays out of the PV products,
+  // where a value that is not finite would make NaN of its zero probabilities)
+  const int k_end = vis_end(r_last, p.La, p.Lp);
+  const int ntiles = ((k_end + kBN - 1) / kBN + RINGS - 1) / RINGS;
   const int ring = SPLIT ? kStages * grp : 0;
   // first concatenated key of this wave's tile t
   auto tile_key = [&](int t) __attribute__((always_inline)) { return (SPLIT ? 2 * t + grp : t) * kBN; };
@@ -688,9 +690,11 @@ attn_fwd_kernel(Params p) {
       softmax_turn(t);
       phase_barrier();
     }
-    mfma_prio();
-    pv_only(ntiles - 1);
-    base_prio();
+    if (tile_key(ntiles - 1) < k_end) {
+      mfma_prio();
+      pv_only(ntiles - 1);
+      base_prio();
+    }
     phase_barrier();
     if (grp == 0) phase_barrier();
     // group B's O, running max and sum through LDS, whose tiles are done with

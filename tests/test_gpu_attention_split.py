@@ -66,3 +66,31 @@ def test_row_form(shape):
 @pytest.mark.parametrize("shape", [SPLIT[9], SPLIT[11], SPLIT[12], WIDE[0], WIDE[1]], ids=str)
 def test_late_max(shape):
     _check(shape, 1.0)
+
+
+@pytest.mark.parametrize("shape", [
+    (2, 1, 0, 700, 1, 4, 1, 64),
+    (4, 3, 50, 600, 40, 4, 1, 64),
+    (4, 3, 50, 600, 40, 2, 1, 128),
+    (1, 0, 0, 700, 0, 2, 1, 128),
+], ids=str)
+@pytest.mark.parametrize("row", [390, 460, -1])
+def test_values_past_the_last_tile_are_not_used(shape, row):
+    # An infinite value makes NaN of the masked products of its 128-key tile,
+    # and of no rows whose 256-row block ends before that tile.
+    torch = need_gpu()
+    p = inputs.Problem(*shape)
+    say(f"[attention forms] {p} infinite value in row {row}")
+    dv = upload(inputs.make_inputs(inputs.Workload("forms", p), seed=41))
+    clean = run_attention(p, dv)
+    row %= p.rows
+    dv["v"][:, row] = float("inf")
+    o, lse = run_attention(p, dv)
+    end = lambda r: (r if r < p.anchor_len else r + p.passing_rows) + 1  # noqa: E731
+    key = end(row) - 1
+    before = [r for r in range(p.rows)
+              if -(-end(min(r // 256 * 256 + 255, p.rows - 1)) // 128) * 128 <= key]
+    assert before
+    assert torch.equal(o[:, before], clean[0][:, before])
+    assert torch.equal(lse, clean[1])
+    assert torch.isinf(o[:, row]).all() or torch.isnan(o[:, row]).all()
