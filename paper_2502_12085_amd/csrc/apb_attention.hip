@@ -48,14 +48,15 @@
 //    the max pass and the O rescale are off the common path.
 //  * Tiles crossing a row's visible end are masked element-wise; tiles past
 //    every row of the workgroup are not visited.
-//  * Problems of few query tiles take a key-split form of the same kernel: both
-//    groups own the same 128 rows and every second key tile each, and merge in
-//    LDS.
+//  * Problems of few query tiles take a key-split form of the same kernel
+//    (apb_plan.h): both groups own the same 128 rows and every second key tile
+//    each, and merge in LDS.
 //  * Grid order puts the query tiles with the longest key prefix first, and
 //    keeps a GQA group's workgroups on one XCD (one L2) when n_kv % 8 == 0.
 #include <math.h>
 
 #include "apb_internal.h"
+#include "apb_plan.h"
 
 namespace apb {
 namespace {
@@ -74,8 +75,8 @@ constexpr int kWaves = 2 * kGroupWaves;     // ping-pong groups A and B
 constexpr int kThreads = 64 * kWaves;
 constexpr int kRowsPerWave = 32;
 constexpr int kBM = kRowsPerWave * kWaves;  // query rows per workgroup
+static_assert(kBM == kAttnRows && kRowsPerWave * kGroupWaves == kAttnSplitRows, "apb_plan.h");
 constexpr int kBN = 128;                           // keys per tile
-constexpr int kSplitBM = kRowsPerWave * kGroupWaves;  // the same of the key-split form
 constexpr int kStages = 2;                         // LDS ring depth for K and V tiles
 constexpr int kPD = 2;                             // LDS operand read-ahead (MFMA steps)
 constexpr int kXcds = 8;                    // MI355X: 8 XCDs, workgroups dealt round-robin
@@ -177,7 +178,7 @@ __device__ __forceinline__ void phase_barrier() {
 template <int D, bool SPLIT>
 __global__ void __launch_bounds__(kThreads, 1)
 attn_fwd_kernel(Params p) {
-  constexpr int BM = SPLIT ? kSplitBM : kBM;     // query rows per workgroup
+  constexpr int BM = SPLIT ? kAttnSplitRows : kBM;     // query rows per workgroup
   constexpr int kBN = SPLIT ? 8192 / D : apb::kBN;  // keys per tile
   constexpr int kKB = kBN / 16;                  // 16-key MFMA blocks per tile
   constexpr int kNPC = kBN / 32;                 // 32-key chunks per tile (PV k-steps)
@@ -814,19 +815,6 @@ attn_fwd_kernel(Params p) {
 
 int attention_tile_rows() { return kBM; }
 
-// The key-split form is for problems whose 256-row workgroups make at most one
-// round: the longest of them is then a serial chain of tiles while CUs idle.
-// Past that the chip is full either way and the 256-row form does less work per
-// key (a K or V tile serves twice the rows).  Measured, 32 / 8 heads of d = 128:
-// 1024 rows and 384 passed keys 48.1 -> 28 us; 1324 rows and 381: 54.0 -> 42.4;
-// 2000 rows (256 workgroups) 55.2 -> 44.4; 2500 rows (320) 68.6 against 69.6;
-// 4096 rows 127 against 140.  d = 64, 4 / 1 heads, 8192 rows (128): 126 -> 79.
-// It needs keys for both groups: 100 rows of d = 64, one tile, 8.2 against 9.1.
-static bool use_split(const Params& p, int head_dim) {
-  const int64_t wgs = ((int64_t)p.M + kBM - 1) / kBM * p.n_q;
-  return wgs <= 256 && p.Ktot > 8192 / head_dim;
-}
-
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
   Params p;
   p.q = a.q; p.k = a.k; p.v = a.v; p.kp = a.kp; p.vp = a.vp; p.o = a.o; p.lse = a.lse;
@@ -836,8 +824,8 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
   p.n_q = a.n_q; p.n_kv = a.n_kv; p.group = a.n_q / a.n_kv;
   p.xcd_map = (p.n_kv % kXcds) == 0;
   p.scale_log2 = a.scale_log2;
-  const bool split = use_split(p, a.head_dim);
-  const int bm = split ? kSplitBM : kBM;
+  const bool split = attention_key_split(p.M, a.La, a.Lp, a.n_q, a.head_dim);
+  const int bm = split ? kAttnSplitRows : kBM;
   p.n_qtiles = (p.M + bm - 1) / bm;
   const dim3 grid((unsigned)(p.n_qtiles * p.n_q));
   if (a.head_dim == 128) {
