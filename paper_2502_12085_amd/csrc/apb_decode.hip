@@ -418,7 +418,7 @@ __global__ void __launch_bounds__(64 * W * KS, (W * KS + 3) / 4) decode_partial_
   float l_tot = l_run + half_swap(l_run);
   if constexpr (KS > 1) {
     // the other groups' O, running max and sum through LDS (the rings are done
-    // with), rescaled to the larger max one after another
+    // with), rescaled to the largest max
     constexpr int OUT = NDB * 16 * 64;  // floats of a wave's O
     static_assert(OUT * W * (KS - 1) * 2 <= KS * RING * BK * D, "merge buffer");
     float* const o_lds = reinterpret_cast<float*>(&k_lds[0][0]) + wave * OUT + lane;
@@ -434,22 +434,34 @@ __global__ void __launch_bounds__(64 * W * KS, (W * KS + 3) / 4) decode_partial_
     }
     __syncthreads();
     if (grp > 0) return;
-    for (int g = 0; g < KS - 1; ++g) {
-      const float m1 = m_lds[g * W * 128], l1 = m_lds[g * W * 128 + 64];
-      const float m = fmaxf(m_run, m1);
-      const float a0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
-      const float a1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
+    // a group without a sum (no keys, or logits that are NaN) has no part in it
+    float mg[KS], lg[KS];
+    mg[0] = m_run;
+    lg[0] = l_tot;
+#pragma unroll
+    for (int g = 1; g < KS; ++g) {
+      mg[g] = m_lds[(g - 1) * W * 128];
+      lg[g] = m_lds[(g - 1) * W * 128 + 64];
+    }
+    m_run = -INFINITY;
+    l_tot = 0.f;
+#pragma unroll
+    for (int g = 0; g < KS; ++g) m_run = fmaxf(m_run, lg[g] > 0.f ? mg[g] : -INFINITY);
+#pragma unroll
+    for (int g = 0; g < KS; ++g) {
+      const float a = lg[g] > 0.f ? __builtin_amdgcn_exp2f(mg[g] - m_run) : 0.f;
+      l_tot += lg[g] > 0.f ? lg[g] * a : 0.f;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          oacc[db][r] = oacc[db][r] * a0 + o_lds[g * W * OUT + 64 * (16 * db + r)] * a1;
-      m_run = m;
-      l_tot = l_tot * a0 + l1 * a1;
+          oacc[db][r] = g == 0 ? oacc[db][r] * a
+                               : fmaf(o_lds[(g - 1) * W * OUT + 64 * (16 * db + r)], a, oacc[db][r]);
     }
   }
   if (!row_ok) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  const bool zero = gridDim.x == 1 && !(l_tot > 0.f);  // the result of no part
   float* orow = p.part_o + ((size_t)split * p.rows_total + grow) * D;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -457,7 +469,7 @@ __global__ void __launch_bounds__(64 * W * KS, (W * KS + 3) / 4) decode_partial_
     for (int g = 0; g < 4; ++g) {
       f32x4 w;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = oacc[db][4 * g + i] * inv;
+      for (int i = 0; i < 4; ++i) w[i] = zero ? 0.f : oacc[db][4 * g + i] * inv;
       *reinterpret_cast<f32x4*>(orow + 32 * db + 8 * g + 4 * h) = w;
     }
   if (h == 0)

@@ -64,3 +64,28 @@ def test_decode_without_keys(d):
     empty = np.zeros((2, 0, d), np.uint16)
     o, lse = _run_decode(q, empty, empty, None, None, 4, 2, d)
     assert (o == 0).all() and np.isneginf(lse).all()
+
+
+@pytest.mark.parametrize("d, cache, n_new, first, last, o_nan", [
+    (128, 20, 2, 3, 3, False),           # one split, which has the NaN
+    (64, 40, 2, 33, 33, False),
+    (128, 100, 1, 3, 3, True),           # one launch, a group of four
+    (64, 250, 3, 100, 100, True),
+    (128, 100, 1, 0, 99, False),         # all of them
+    (64, 250, 3, 0, 249, False),
+    (128, 4000, 25, 100, 100, True),     # 100 rows: two groups, one with the NaN
+])
+def test_decode_with_nan_keys(d, cache, n_new, first, last, o_nan):
+    # A part of the keys whose logits are NaN has no LSE.  It is no part of the
+    # row's LSE, and the row's output is NaN unless no other part is left: then
+    # it is that of a host without keys.
+    n_q, n_kv = 8, 2
+    say(f"[decode groups] NaN in keys {first} to {last} of {cache}, d {d}")
+    case = inputs.make_decode_case(n_q, n_kv, d, [cache], n_new, seed=5)
+    kc, vc = case["caches"][0]
+    kc[:, first:last + 1] = 0x7fc0
+    o, lse = _run_decode(case["q"], kc, vc, None, None, n_q, n_kv, d)
+    if o_nan:
+        assert np.isnan(o).all() and np.isfinite(lse).all()
+    else:
+        assert (o == 0).all() and np.isneginf(lse).all()
