@@ -42,6 +42,7 @@
 #include <mutex>
 
 #include "apb_internal.h"
+#include "apb_plan.h"
 
 namespace apb {
 namespace {
@@ -55,19 +56,10 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 
-constexpr int kRows = 32;   // rows per workgroup (the MFMA N side)
-constexpr int kKeys = 32;   // keys per MFMA block (the MFMA M side)
-constexpr int kWgPerCu = 3; // one-wave workgroups per CU (LDS: 3 x 48 KiB at d = 128)
 constexpr int kRing = 3;    // LDS stages of K and V blocks per one-wave workgroup
 constexpr int kGroupRing = 4;  // LDS stages of each of the two groups of a four-wave workgroup
-// The one-launch form, for few keys: that many one-wave groups per workgroup
-// (two stages each in 128 KiB of LDS), at most that many key blocks.  The step is
-// then launches and latency: against split and merge, 32 / 8 heads of d = 128,
-// one token: 100 keys 9.7 -> 6.9 us, 250 9.8 -> 8.0, 500 (16 blocks) 9.8 against
-// 9.6, 750 9.7 against 11.1; 4 / 1 heads of d = 64: 500 keys 9.6 -> 6.6, 1000 (32
-// blocks) 9.7 -> 7.9, 2000 9.7 against 10.5.
+// One-wave groups of a one-launch workgroup (two stages each in 128 KiB of LDS).
 constexpr int one_launch_groups(int d) { return d == 128 ? 4 : 8; }
-constexpr int one_launch_blocks(int d) { return d == 128 ? 12 : 32; }
 constexpr float kSumLimit = 8192.f;  // lazy rescale: largest block row-half sum against a stale max
 
 struct DecParams {
@@ -138,7 +130,7 @@ __device__ __forceinline__ const uint16_t* kv_row(const DecParams& p, const uint
 // Keys per tile of the eight-wave kernel: four 32-key MFMA blocks, so that a
 // phase holds 64 MFMAs (the most the registers allow, as in the prefill
 // kernel) and its QK products run as four independent accumulator chains.
-constexpr int kPingPongKB = 4;
+constexpr int kPingPongKB = kTileBlocks;
 
 // Fewer rows per KV head, up to 32 * W.  W = 1 (one generated token, and up to 64
 // rows as two workgroups): a one-wave workgroup owns the 32-row block blockIdx.z
@@ -965,63 +957,7 @@ hipError_t launch_merge_t(int n_parts, int rows, int d, const PartT* o_parts,
 }  // namespace
 
 DecodePlan plan_decode(const DecodeArgs& a, uint64_t max_workspace_bytes) {
-  DecodePlan pl;
-  const int64_t keys = (int64_t)a.Lc + (a.append ? a.n_new : 0);
-  const int64_t R = (int64_t)(a.n_q / a.n_kv) * a.n_new;
-  // A GQA group of at least four 32-row blocks shares each K/V tile among the 8
-  // waves of a workgroup (one workgroup per CU: its registers), else one wave
-  // per 32-row block (kWgPerCu per CU: their LDS).
-  pl.waves = R >= 4 * kRows ? 8 : 1;
-  const int64_t bk = pl.waves == 8 ? kPingPongKB * kKeys : kKeys;
-  const int64_t nblk = (keys + bk - 1) / bk;
-  int64_t n_rb = (R + kRows * pl.waves - 1) / (kRows * pl.waves);
-  // one round of workgroups, at least two key blocks each
-  const int64_t target = pl.waves == 1 ? 256 * kWgPerCu : 256;
-  int64_t n_split = target / (a.n_kv * n_rb);
-  if (n_split > nblk / 2) n_split = nblk / 2;
-  if (n_split < 1) n_split = 1;
-  int64_t bps = nblk > 0 ? (nblk + n_split - 1) / n_split : 0;
-  if (bps > 0) n_split = (nblk + bps - 1) / bps;
-  // Three or four row blocks: the same splits, but two groups of four waves per
-  // workgroup in place of a workgroup per row block, each reading the keys
-  // again (85 rows x 30001 keys x 8 heads of d = 128: 40.7 -> 31.7 us; 124 rows
-  // x 16384: 30.9 -> 25.6).  Splits of fewer than four blocks are too short for
-  // the groups' merge (124 rows x 1000: 13.5 -> 14.7 us).  With two row blocks
-  // the second read comes from cache and the groups gain nothing.
-  if (pl.waves == 1 && n_rb > 2 && bps >= 4) {
-    pl.waves = 4;
-    n_rb = 1;
-  }
-  // a workspace limit caps the splits (longer splits, the same kernels)
-  const int64_t rows_total = (int64_t)a.n_q * a.n_new;
-  // per (split, row): fp32 O and LSE, or fp16 O, its scale and the LSE
-  const uint64_t per_row = pl.waves == 8 ? (uint64_t)a.head_dim * 2 + 8 : (uint64_t)(a.head_dim + 1) * 4;
-  const uint64_t per_split = (uint64_t)rows_total * per_row;
-  if ((uint64_t)n_split * per_split > max_workspace_bytes) {
-    const int64_t cap = (int64_t)(max_workspace_bytes / per_split);
-    if (cap < 1) {
-      pl.n_split = 0;  // does not fit
-      pl.one_launch = false;
-      pl.blocks_per_split = 0;
-      pl.row_blocks = (int)n_rb;
-      pl.workspace_bytes = per_split;
-      return pl;
-    }
-    bps = (nblk + cap - 1) / cap;
-    n_split = (nblk + bps - 1) / bps;
-  }
-  pl.workspace_bytes = (uint64_t)n_split * per_split;
-  pl.one_launch = false;
-  // (the workspace keeps the size of the splits)
-  if (pl.waves == 1 && n_split > 1 && nblk <= one_launch_blocks(a.head_dim)) {
-    pl.one_launch = true;
-    n_split = 1;
-    bps = nblk;
-  }
-  pl.n_split = (int)n_split;
-  pl.blocks_per_split = (int)bps;
-  pl.row_blocks = (int)n_rb;
-  return pl;
+  return plan_decode(a.n_q, a.n_kv, a.head_dim, a.Lc, a.n_new, a.append, max_workspace_bytes);
 }
 
 // Device scratch of the no-allocation entry point: one array per GPU (each

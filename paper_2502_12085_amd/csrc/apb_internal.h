@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "apb_plan.h"
+
 namespace apb {
 
 // One host share, already validated.  Row counts are the paper's:
@@ -49,18 +51,6 @@ struct DecodeArgs {
   int32_t Lc, n_new, append;
   int32_t n_q, n_kv, head_dim;
   float scale_log2;
-};
-
-// How a decode call splits its keys; the workspace holds one partial per
-// split and row: fp32 O and LSE (one or four row blocks), or fp16 O with a
-// per-row power-of-two scale and the LSE (eight).
-struct DecodePlan {
-  int n_split;
-  int blocks_per_split;
-  int row_blocks;      // workgroups along the rows (each waves * 32 rows)
-  int waves;           // 32-row blocks of a workgroup that share its key blocks (1, 4 or 8)
-  bool one_launch;     // few keys: one split, its key blocks shared among a workgroup's waves
-  uint64_t workspace_bytes;
 };
 
 struct MergeArgs {

@@ -51,6 +51,93 @@ inline bool attention_key_split(int64_t M, int64_t La, int64_t Lp, int64_t n_q, 
   return 384 * (total + second + fixed) <= rate * total;
 }
 
+// How a decode call splits its keys; the workspace holds one partial per
+// split and row: fp32 O and LSE (one or four row blocks), or fp16 O with a
+// per-row power-of-two scale and the LSE (eight).
+struct DecodePlan {
+  int n_split;
+  int blocks_per_split;
+  int row_blocks;      // workgroups along the rows (each waves * 32 rows)
+  int waves;           // 32-row blocks of a workgroup that share its key blocks (1, 4 or 8)
+  bool one_launch;     // few keys: one split, its key blocks shared among a workgroup's waves
+  uint64_t workspace_bytes;
+};
+
+// Rows and keys of a decode MFMA block, and the 32-key blocks of an eight-wave
+// workgroup's tile.
+constexpr int kRows = 32;
+constexpr int kKeys = 32;
+constexpr int kTileBlocks = 4;
+constexpr int kWgPerCu = 3;  // one-wave workgroups per CU (LDS: 3 x 48 KiB at d = 128)
+
+// Most key blocks of the one-launch form, whose waves share them: the step is then
+// launches and latency.  Against split and merge, 32 / 8 heads of d = 128: 4 blocks
+// 8.9 -> 6.9 us, 8 8.6 -> 7.9, 12 8.6 -> 8.5, 16 9.6 against 9.8 (turns of four
+// blocks); 4 / 1 heads of d = 64: 4 blocks 7.0 -> 4.9, 20 7.2 -> 6.2, 28 7.1 ->
+// 7.0, 30 7.0 against 7.7 (turns of eight, and the next splits are longer at 32).
+constexpr int one_launch_blocks(int d) { return d == 128 ? 12 : 28; }
+
+// max_workspace_bytes caps the splits; a plan with n_split == 0 does not fit.
+inline DecodePlan plan_decode(int64_t n_q, int64_t n_kv, int head_dim, int64_t cache_len,
+                              int64_t n_new, bool append, uint64_t max_workspace_bytes) {
+  DecodePlan pl;
+  const int64_t keys = cache_len + (append ? n_new : 0);
+  const int64_t R = n_q / n_kv * n_new;
+  // A GQA group of at least four 32-row blocks shares each K/V tile among the 8
+  // waves of a workgroup (one workgroup per CU: its registers), else one wave
+  // per 32-row block (kWgPerCu per CU: their LDS).
+  pl.waves = R >= 4 * kRows ? 8 : 1;
+  const int64_t bk = pl.waves == 8 ? kTileBlocks * kKeys : kKeys;
+  const int64_t nblk = (keys + bk - 1) / bk;
+  int64_t n_rb = (R + kRows * pl.waves - 1) / (kRows * pl.waves);
+  // one round of workgroups, at least two key blocks each
+  const int64_t target = pl.waves == 1 ? kCus * kWgPerCu : kCus;
+  int64_t n_split = target / (n_kv * n_rb);
+  if (n_split > nblk / 2) n_split = nblk / 2;
+  if (n_split < 1) n_split = 1;
+  int64_t bps = nblk > 0 ? (nblk + n_split - 1) / n_split : 0;
+  if (bps > 0) n_split = (nblk + bps - 1) / bps;
+  // Three or four row blocks: the same splits, but two groups of four waves per
+  // workgroup in place of a workgroup per row block, each reading the keys
+  // again (85 rows x 30001 keys x 8 heads of d = 128: 40.7 -> 31.7 us; 124 rows
+  // x 16384: 30.9 -> 25.6).  Splits of fewer than four blocks are too short for
+  // the groups' merge (124 rows x 1000: 13.5 -> 14.7 us).  With two row blocks
+  // the second read comes from cache and the groups gain nothing.
+  if (pl.waves == 1 && n_rb > 2 && bps >= 4) {
+    pl.waves = 4;
+    n_rb = 1;
+  }
+  // a workspace limit caps the splits (longer splits, the same kernels)
+  const int64_t rows_total = n_q * n_new;
+  // per (split, row): fp32 O and LSE, or fp16 O, its scale and the LSE
+  const uint64_t per_row = pl.waves == 8 ? (uint64_t)head_dim * 2 + 8 : (uint64_t)(head_dim + 1) * 4;
+  const uint64_t per_split = (uint64_t)rows_total * per_row;
+  pl.one_launch = false;
+  if ((uint64_t)n_split * per_split > max_workspace_bytes) {
+    const int64_t cap = (int64_t)(max_workspace_bytes / per_split);
+    if (cap < 1) {
+      pl.n_split = 0;  // does not fit
+      pl.blocks_per_split = 0;
+      pl.row_blocks = (int)n_rb;
+      pl.workspace_bytes = per_split;
+      return pl;
+    }
+    bps = (nblk + cap - 1) / cap;
+    n_split = (nblk + bps - 1) / bps;
+  }
+  pl.workspace_bytes = (uint64_t)n_split * per_split;
+  // (the workspace keeps the size of the splits)
+  if (pl.waves == 1 && n_split > 1 && nblk <= one_launch_blocks(head_dim)) {
+    pl.one_launch = true;
+    n_split = 1;
+    bps = nblk;
+  }
+  pl.n_split = (int)n_split;
+  pl.blocks_per_split = (int)bps;
+  pl.row_blocks = (int)n_rb;
+  return pl;
+}
+
 }  // namespace apb
 
 #endif  // APB_PLAN_H_

@@ -16,14 +16,17 @@ from test_gpu_decode import _run_decode
 pytestmark = pytest.mark.gpu
 
 
+# n_q, n_kv, d, Lc, n_new, append; softmax scale
 ONE_LAUNCH = [
     ((8, 2, 128, 127, 1, 1), 0.0),       # four blocks, one per group
     ((8, 2, 128, 150, 3, 0), 0.0),       # five: the second turn is one group's
     ((32, 8, 128, 383, 1, 1), 0.0),      # 12 blocks
     ((32, 8, 128, 384, 1, 1), 0.0),      # 13: split and merge
     ((4, 1, 64, 97, 2, 1), 0.0),         # four blocks, four groups without any
-    ((4, 1, 64, 1022, 2, 1), 0.0),       # 32 blocks
-    ((4, 1, 64, 1023, 2, 1), 0.0),       # 33: split and merge
+    ((4, 1, 64, 894, 2, 1), 0.0),        # 28 blocks
+    ((4, 1, 64, 895, 2, 1), 0.0),        # 29: split and merge
+    ((4, 1, 64, 1022, 2, 1), 0.0),       # 32
+    ((4, 1, 64, 1023, 2, 1), 0.0),       # 33
     ((10, 2, 64, 700, 10, 1), 0.0),      # 50 rows: two row blocks
     ((24, 2, 128, 200, 10, 0), 0.0),     # 120 rows in four row blocks
     ((8, 2, 128, 40, 1, 1), 0.0),        # two blocks: one split of one group
@@ -32,8 +35,7 @@ ONE_LAUNCH = [
 ]
 
 
-@pytest.mark.parametrize("shape, scale", ONE_LAUNCH + [
-    # n_q, n_kv, d, Lc, n_new, append
+GROUPS = [
     ((32, 16, 64, 2100, 33, 1), 0.0),    # 66 rows: the third row block has two
     ((48, 16, 128, 2500, 25, 0), 0.0),   # 75 rows, 79 blocks in splits of 5
     ((64, 16, 128, 2049, 31, 1), 0.0),   # 124 rows: four row blocks
@@ -42,7 +44,10 @@ ONE_LAUNCH = [
     ((127, 127, 64, 200, 100, 1), 0.0),  # one split per head, new tokens longer than a block
     ((32, 16, 128, 2100, 33, 1), 1.0),
     ((8, 2, 64, 15990, 31, 1), 1.0),
-])
+]
+
+
+@pytest.mark.parametrize("shape, scale", ONE_LAUNCH + GROUPS)
 def test_decode_wave_groups(shape, scale):
     need_gpu()
     n_q, n_kv, d, lc, n_new, app = shape

@@ -7,6 +7,8 @@ import subprocess
 import pytest
 
 import test_gpu_attention_split as attention_forms
+import test_gpu_decode_groups as decode_forms
+from paper_2502_12085_amd import apb
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                     "paper_2502_12085_amd", "csrc")
@@ -21,6 +23,11 @@ int main() {
     if (!strcmp(rule, "attention")) {
       for (int i = 0; i < 5; ++i) if (scanf("%lld", &a[i]) != 1) return 1;
       printf("%d\n", (int)apb::attention_key_split(a[0], a[1], a[2], a[3], a[4]));
+    } else if (!strcmp(rule, "decode")) {
+      for (int i = 0; i < 7; ++i) if (scanf("%lld", &a[i]) != 1) return 1;
+      const apb::DecodePlan p = apb::plan_decode(a[0], a[1], (int)a[2], a[3], a[4], a[5] != 0, a[6]);
+      printf("%d %d %d %d %d %llu\n", p.waves, p.one_launch, p.n_split, p.blocks_per_split,
+             p.row_blocks, (unsigned long long)p.workspace_bytes);
     } else {
       return 1;
     }
@@ -89,3 +96,54 @@ def test_attention_forms_of_the_gpu_tests(plan):
 ])
 def test_attention_form(plan, shape, split):
     assert _key_split(plan, *shape) == split
+
+
+NO_LIMIT = 1 << 62
+
+
+def _decode(plan, n_q, n_kv, d, lc, n_new, app, limit=NO_LIMIT):
+    waves, one, n_split, bps, rb, ws = plan("decode", n_q, n_kv, d, lc, n_new, app, limit)
+    assert ws == apb.decode_workspace_size(apb.DecodeProblem(n_q, n_kv, d, lc, n_new, app)) \
+        or limit != NO_LIMIT
+    return ("one launch" if one else waves), n_split, bps
+
+
+def test_decode_forms_of_the_gpu_tests(plan):
+    for s, _ in decode_forms.ONE_LAUNCH:
+        blocks = -(-(s[3] + s[4] * s[5]) // 32)
+        got = _decode(plan, *s)[0]
+        if s == (24, 2, 128, 200, 10, 0):
+            assert got == "one launch"  # 120 rows, splits too short for groups
+        elif s == (8, 2, 128, 40, 1, 1):
+            assert got == 1             # one split
+        else:
+            assert (got == "one launch") == (blocks <= (12 if s[2] == 128 else 28)), s
+    for s, _ in decode_forms.GROUPS:
+        assert _decode(plan, *s)[0] == 4, s
+
+
+@pytest.mark.parametrize("shape, form", [
+    # n_q, n_kv, d, Lc, n_new, append: the one-launch form's last length
+    ((32, 8, 128, 383, 1, 1), "one launch"),
+    ((32, 8, 128, 384, 1, 1), 1),
+    ((56, 8, 128, 376, 8, 1), "one launch"),
+    ((4, 1, 64, 895, 1, 1), "one launch"),
+    ((4, 1, 64, 896, 1, 1), 1),
+    ((8, 2, 64, 950, 2, 1), 1),
+    # many rows
+    ((32, 8, 128, 16384, 32, 1), 8),
+    ((32, 8, 128, 16384, 31, 1), 4),
+    ((32, 8, 128, 16384, 16, 1), 1),
+])
+def test_decode_form(plan, shape, form):
+    assert _decode(plan, *shape)[0] == form
+
+
+def test_decode_plan_within_a_limit(plan):
+    # one part per split of (d + 1) floats per row; the one-launch form needs the
+    # scratch of the splits all the same, and gives way to a single split
+    part = 8 * 1 * 129 * 4
+    assert _decode(plan, 8, 2, 128, 300, 1, 1, part - 1)[1] == 0
+    assert _decode(plan, 8, 2, 128, 300, 1, 1, part) == (1, 1, 10)
+    assert _decode(plan, 8, 2, 128, 300, 1, 1, 2 * part) == ("one launch", 1, 10)
+    assert _decode(plan, 8, 2, 128, 8000, 1, 1, 3 * part) == (1, 3, 84)
