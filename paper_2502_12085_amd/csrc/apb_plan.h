@@ -97,13 +97,17 @@ inline DecodePlan plan_decode(int64_t n_q, int64_t n_kv, int head_dim, int64_t c
   if (n_split < 1) n_split = 1;
   int64_t bps = nblk > 0 ? (nblk + n_split - 1) / n_split : 0;
   if (bps > 0) n_split = (nblk + bps - 1) / bps;
-  // Three or four row blocks: the same splits, but two groups of four waves per
-  // workgroup in place of a workgroup per row block, each reading the keys
-  // again (85 rows x 30001 keys x 8 heads of d = 128: 40.7 -> 31.7 us; 124 rows
-  // x 16384: 30.9 -> 25.6).  Splits of fewer than four blocks are too short for
-  // the groups' merge (124 rows x 1000: 13.5 -> 14.7 us).  With two row blocks
-  // the second read comes from cache and the groups gain nothing.
-  if (pl.waves == 1 && n_rb > 2 && bps >= 4) {
+  // Three or four row blocks: the same splits (256 workgroups, or 192 with four),
+  // but two groups of four waves per workgroup in place of a workgroup per row
+  // block, each reading the keys again.  85 rows x 30001 keys x 8 heads of d = 128:
+  // 39.5 -> 31.7 us; 124 rows x 16384: 30.9 -> 25.6.  Short splits end before the
+  // groups' start and merge are made up for.  By blocks per split, three row
+  // blocks of d = 128 (96 rows x 8 heads): 4 18.7 against 19.3 us, 6 19.0 against
+  // 20.0, 8 20.3 -> 20.2, 12 23.6 -> 22.5; four (124 rows): 4 18.6 against 19.3, 6
+  // 20.4 against 20.5, 8 22.0 -> 21.8; d = 64 (124 rows x 2 heads): 4 14.0 against
+  // 14.4, 6 15.5 -> 15.3.  With two row blocks the second read comes from cache
+  // and the groups gain nothing.
+  if (pl.waves == 1 && n_rb > 2 && bps >= (head_dim == 128 ? 9 : 6)) {
     pl.waves = 4;
     n_rb = 1;
   }

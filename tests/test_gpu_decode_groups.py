@@ -36,18 +36,26 @@ ONE_LAUNCH = [
 
 
 GROUPS = [
-    ((32, 16, 64, 2100, 33, 1), 0.0),    # 66 rows: the third row block has two
-    ((48, 16, 128, 2500, 25, 0), 0.0),   # 75 rows, 79 blocks in splits of 5
-    ((64, 16, 128, 2049, 31, 1), 0.0),   # 124 rows: four row blocks
-    ((40, 8, 128, 4500, 17, 1), 0.0),    # 85 rows, GQA 5
+    ((32, 16, 64, 3200, 33, 1), 0.0),    # 66 rows: the third row block has two
+    ((48, 16, 128, 5000, 25, 0), 0.0),   # 75 rows, 157 blocks in splits of 10
+    ((64, 16, 128, 4400, 31, 1), 0.0),   # 124 rows: four row blocks
+    ((40, 8, 128, 9300, 17, 1), 0.0),    # 85 rows, GQA 5, last split of two blocks
     ((14, 2, 64, 15380, 18, 0), 0.0),    # 126 rows, two heads, last split of one block
     ((127, 127, 64, 200, 100, 1), 0.0),  # one split per head, new tokens longer than a block
-    ((32, 16, 128, 2100, 33, 1), 1.0),
+    ((32, 16, 128, 5000, 33, 1), 1.0),
     ((8, 2, 64, 15990, 31, 1), 1.0),
+]
+# As many rows over shorter splits: a workgroup per row block.
+SHORT = [
+    ((32, 16, 64, 2100, 33, 1), 0.0),
+    ((48, 16, 128, 2500, 25, 0), 0.0),
+    ((64, 16, 128, 2049, 31, 1), 0.0),
+    ((40, 8, 128, 4500, 17, 1), 0.0),
+    ((32, 16, 128, 2100, 33, 1), 1.0),
 ]
 
 
-@pytest.mark.parametrize("shape, scale", ONE_LAUNCH + GROUPS)
+@pytest.mark.parametrize("shape, scale", ONE_LAUNCH + GROUPS + SHORT)
 def test_decode_wave_groups(shape, scale):
     need_gpu()
     n_q, n_kv, d, lc, n_new, app = shape
@@ -78,7 +86,7 @@ def test_decode_without_keys(d):
     (64, 250, 3, 100, 100, True),
     (128, 100, 1, 0, 99, False),         # all of them
     (64, 250, 3, 0, 249, False),
-    (128, 4000, 25, 100, 100, True),     # 100 rows: two groups, one with the NaN
+    (128, 36000, 25, 100, 100, True),    # 100 rows: two groups, one with the NaN
 ])
 def test_decode_with_nan_keys(d, cache, n_new, first, last, o_nan):
     # A part of the keys whose logits are NaN has no LSE.  It is no part of the

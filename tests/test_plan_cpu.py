@@ -120,6 +120,9 @@ def test_decode_forms_of_the_gpu_tests(plan):
             assert (got == "one launch") == (blocks <= (12 if s[2] == 128 else 28)), s
     for s, _ in decode_forms.GROUPS:
         assert _decode(plan, *s)[0] == 4, s
+    for s, _ in decode_forms.SHORT:
+        assert _decode(plan, *s)[0] == 1, s
+    assert _decode(plan, 8, 2, 128, 36000, 25, 0)[0] == 4  # its NaN test
 
 
 @pytest.mark.parametrize("shape, form", [
@@ -133,6 +136,15 @@ def test_decode_forms_of_the_gpu_tests(plan):
     # many rows
     ((32, 8, 128, 16384, 32, 1), 8),
     ((32, 8, 128, 16384, 31, 1), 4),
+    # three and four row blocks: splits of 8 and 9 blocks of d = 128, 5 and 6 of 64
+    ((32, 8, 128, 8150, 24, 1), 1),
+    ((32, 8, 128, 8200, 24, 1), 4),
+    ((32, 8, 128, 6100, 31, 1), 1),
+    ((32, 8, 128, 6150, 31, 1), 4),
+    ((8, 2, 64, 20400, 24, 1), 1),
+    ((8, 2, 64, 20600, 24, 1), 4),
+    ((8, 2, 64, 15300, 31, 1), 1),
+    ((8, 2, 64, 15400, 31, 1), 4),
     ((32, 8, 128, 16384, 16, 1), 1),
 ])
 def test_decode_form(plan, shape, form):
