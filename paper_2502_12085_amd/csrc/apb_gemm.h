@@ -192,38 +192,45 @@ gemm_kernel(GemmParams p) {
   const uint16_t* const w_first = p.w + (size_t)f0 * p.K;
   const uint16_t* const w_up_first = (WM == kWGateUp ? p.w_up : p.w) + (size_t)f0 * p.K;
   const uint16_t* const x_first = p.x + (size_t)t0 * x_ld;
-  // copy q (0..CPS-1) of step kk into stage st: q < 8 weight pieces, else token pieces
-  auto copy = [&](int kk, int st, int q) __attribute__((always_inline)) {
+  // First token row's K elements of step kk.  Formed once per step and without
+  // branches: the compiler put the choice of the Q, K or V tensor into branches
+  // among the copies of the two-barrier loop (32768 tokens x 1024 units at K =
+  // 9216: 541 against 442 us).
+  auto token_base = [&](int kk) __attribute__((always_inline)) -> const uint16_t* {
     const int k0 = kk * kBK;
+    if constexpr (XM == kXRowMajor) {
+      return x_first + k0;
+    } else {
+      // head-major tokens: K element k0 is column k0 % dh of head k0 / dh
+      const int head = k0 >> dh_shift, j0 = k0 - (head << dh_shift);
+      if constexpr (XM == kXQkv) {
+        // with masks: a branch here makes the step wait for all operand reads
+        const int in_kv = -(int)(head >= p.n_q), in_v = -(int)(head >= p.n_q + p.n_kv);
+        const int hh = head - (p.n_q & in_kv) - (p.n_kv & in_v);
+        const int64_t src = (int64_t)p.x + (((int64_t)p.x_k - (int64_t)p.x) & in_kv) +
+                            (((int64_t)p.x_v - (int64_t)p.x_k) & in_v);
+        return (const uint16_t*)src + ((size_t)hh * p.x_rows + p.x_row0 + t0) * p.dh + j0;
+      } else {
+        return x_first + (size_t)head * p.T * p.dh + j0;
+      }
+    }
+  };
+  // copy q (0..CPS-1) of step kk, with its token_base, into stage st: q < 8
+  // weight pieces, else token pieces
+  auto copy = [&](int kk, const uint16_t* xb, int st, int q) __attribute__((always_inline)) {
     if (q < kPieces) {
       const int i = q, j = kPieces * wave + i;
       // gate/up: rows 64..127 of either 128-row half are up-projection rows
       const uint16_t* base =
-          (WM == kWGateUp && ((kPieces * wave + i) & 15) >= 8 ? w_up_first : w_first) + k0;
+          (WM == kWGateUp && ((kPieces * wave + i) & 15) >= 8 ? w_up_first : w_first) + kk * kBK;
       const uint32_t d = __builtin_amdgcn_readfirstlane(lds_offset(&a_lds[st][j * 512]));
       asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(w_off[i]), "s"(base),
                    "s"(d)
                    : "memory");
     } else {
       const int i = q - kPieces, j = NB * wave + i;
-      const uint16_t* base;
-      if constexpr (XM == kXRowMajor) {
-        base = x_first + k0;
-      } else {
-        // head-major tokens: K element k0 is column k0 % dh of head k0 / dh
-        const int head = k0 >> dh_shift, j0 = k0 - (head << dh_shift);
-        if constexpr (XM == kXQkv) {
-          const uint16_t* src = head < p.n_q ? p.x : head < p.n_q + p.n_kv ? p.x_k : p.x_v;
-          const int hh = head < p.n_q ? head
-                         : head < p.n_q + p.n_kv ? head - p.n_q
-                                                 : head - p.n_q - p.n_kv;
-          base = src + ((size_t)hh * p.x_rows + p.x_row0 + t0) * p.dh + j0;
-        } else {
-          base = x_first + (size_t)head * p.T * p.dh + j0;
-        }
-      }
       const uint32_t d = __builtin_amdgcn_readfirstlane(lds_offset(&b_lds[st][j * 512]));
-      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(x_off[i]), "s"(base),
+      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(x_off[i]), "s"(xb),
                    "s"(d)
                    : "memory");
     }
@@ -235,8 +242,9 @@ gemm_kernel(GemmParams p) {
 #pragma unroll
     for (int k0 = 0; k0 < NST; ++k0) {
       if (k0 < nk) {
+        const uint16_t* const xb = token_base(k0);
 #pragma unroll
-        for (int q = 0; q < CPS; ++q) copy(k0, k0, q);
+        for (int q = 0; q < CPS; ++q) copy(k0, xb, k0, q);
       }
     }
     if (nk >= NST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * CPS) : "memory");
@@ -257,8 +265,9 @@ gemm_kernel(GemmParams p) {
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         asm volatile("s_barrier" ::: "memory");
         if (kk + NST < nk) {
+          const uint16_t* const xb = token_base(kk + NST);
 #pragma unroll
-          for (int q = 0; q < CPS; ++q) copy(kk + NST, st, q);
+          for (int q = 0; q < CPS; ++q) copy(kk + NST, xb, st, q);
         }
         st = st + 1 == NST ? 0 : st + 1;
       }
@@ -312,7 +321,12 @@ gemm_kernel(GemmParams p) {
       for (int r = 0; r < 4; ++r) acc[mb][nb][r] = 0.f;
   bf16x8 av[2][8], bv[2][NB];
 
-  // step 0 is visible: its first operands
+  // step 0 is visible: its first operands.  Scalar loads (the epilogue's
+  // pointers, loaded early) are waited for first: they complete in no order, so
+  // one that may be pending at the loop's entry makes its first MFMA wait for all
+  // operand reads in flight, in every step (32768 tokens x 1024 units at K = 9216:
+  // 475 against 465 us).
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0) alone
 #pragma unroll
   for (int mb = 0; mb < 8; ++mb) av[0][mb] = read(a_base(0), mb, 0);
 #pragma unroll
@@ -335,6 +349,7 @@ gemm_kernel(GemmParams p) {
     constexpr bool NEXT = decltype(next_t)::value, COPY = decltype(copy_t)::value && !SPLIT;
     const int st1 = st + 1 == NST ? 0 : st + 1;
     const uint32_t ab = a_base(st), bb = b_base(st), ab1 = a_base(st1), bb1 = b_base(st1);
+    const uint16_t* const xb = COPY ? token_base(kk + 2) : nullptr;
 #pragma unroll
     for (int kc = 0; kc < 2; ++kc) {
       const int cur = kc, nxt = kc ^ 1;
@@ -368,11 +383,11 @@ gemm_kernel(GemmParams p) {
         }
         if constexpr (COPY && EARLY) {
           if ((i & 3) == 0) {
-            if (!boundary && i >= 48) copy(kk + 2, st, (i - 48) >> 2);
-            else if (boundary && i < 48) copy(kk + 2, st, 4 + (i >> 2));
+            if (!boundary && i >= 48) copy(kk + 2, xb, st, (i - 48) >> 2);
+            else if (boundary && i < 48) copy(kk + 2, xb, st, 4 + (i >> 2));
           }
         } else if constexpr (COPY) {
-          if (boundary && (i & 3) == 0) copy(kk + 2, st, i >> 2);
+          if (boundary && (i & 3) == 0) copy(kk + 2, xb, st, i >> 2);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
