@@ -53,9 +53,11 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const uint16_t* __restrict
 // and its cosine and sine are computed in fp64 (positions reach 10^5, where an
 // fp32 angle would lose its fraction), the rotation in fp32.  A workgroup takes
 // 512 / dh rows: each thread the cosine and sine of one (row, j), into LDS, then
-// four pairs of a row and head at a time, four such quads in flight.  10240 rows
-// of Llama-3.1-8B, 210 MB: 44.8 -> 36.4 us against one pair per thread walking
-// all heads; 1256 rows, bound by latency, 17.7 -> 11.8.
+// four pairs of a row and head at a time, four such quads in flight.  The fused
+// products are written out: which of a sum's two the compiler fuses, and so the
+// last bit, would be its choice.  10240 rows of Llama-3.1-8B, 210 MB: 44.8 -> 36.4
+// us against one pair per thread walking all heads; 1256 rows, bound by latency,
+// 17.7 -> 11.8.
 __global__ void __launch_bounds__(256) rope_kernel(uint16_t* __restrict__ q,
                                                    uint16_t* __restrict__ k,
                                                    const int32_t* __restrict__ pos, int T,
@@ -100,8 +102,8 @@ __global__ void __launch_bounds__(256) rope_kernel(uint16_t* __restrict__ q,
       for (int e = 0; e < 4; ++e) {
         const float c = cs[cj[u] + e], s = sn[cj[u] + e];
         const float x = (float)lo[u][e], y = (float)hi[u][e];
-        a[e] = (__bf16)(x * c - y * s);
-        b[e] = (__bf16)(y * c + x * s);
+        a[e] = (__bf16)fmaf(x, c, -(y * s));
+        b[e] = (__bf16)fmaf(x, s, y * c);
       }
       *reinterpret_cast<bf16x4*>(at[u]) = a;
       *reinterpret_cast<bf16x4*>(at[u] + half) = b;

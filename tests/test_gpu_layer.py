@@ -30,7 +30,7 @@ ATOL, RTOL, MEAN_ABS = 0.02, 0.01, 4e-3
 SCORE_TOL = 0.05
 
 
-def _run_layer(lw, seed=0):
+def _run_layer(lw, seed=0, pos=None):
     torch = need_gpu()
     from paper_2502_12085_amd import apb
     p = lw.problem
@@ -44,7 +44,7 @@ def _run_layer(lw, seed=0):
     for name, key in (("r_b1", "b1"), ("r_w2", "w2"), ("r_b2", "b2")):
         w[name] = torch.from_numpy(np.ascontiguousarray(inp["w"][key])).cuda()
     hidden = dev_bf16(inp["hidden"])
-    pos = torch.from_numpy(inp["pos"]).cuda()
+    pos = torch.from_numpy(inp["pos"] if pos is None else pos).cuda()
     # rank-major passing buffers; the slots from host_idx on start as a NaN guard
     pk = torch.full((p.n_hosts, nkv, p.pass_len, d), float("nan"), dtype=torch.bfloat16,
                     device="cuda")
@@ -165,3 +165,26 @@ def test_llama8b_128k_layer_sampled_rows():
     _close(host_bf16_to_f64(got["k"]), ref["k"], "K cache (post-RoPE)")
     _close(host_bf16_to_f64(got["v"]), ref["v"], "V cache")
     _check_selection(lw, inp, got, ref)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_rope_rounding(d):
+    # The rotation of (x, y) rounds in fp32 as fma(x, c, -(y s)) and
+    # fma(x, s, y c), then to bf16: bit for bit, with the unrotated K taken
+    # from the same layer at position 0.
+    lw = _tiny_variant(f"rope_{d}", n_q_heads=4, n_kv_heads=4, head_dim=d, anchor_len=500,
+                       local_len=5501, host_idx=1, pass_len=10)
+    say(f"[layer] rotation of {lw.problem.rows} rows of d {d}")
+    inp, got = _run_layer(lw)
+    _, flat = _run_layer(lw, pos=np.zeros_like(inp["pos"]))
+    k0 = host_bf16_to_f64(flat["k"])
+    x, y = k0[..., :d // 2], k0[..., d // 2:]
+    ang = inp["pos"].astype(np.float64)[:, None] * np.exp(
+        -2.0 * np.arange(d // 2) / d * np.log(np.float64(np.float32(lw.theta))))
+    c, s = (f(ang).astype(np.float32).astype(np.float64) for f in (np.cos, np.sin))
+    f32 = lambda a: a.astype(np.float32).astype(np.float64)  # noqa: E731
+    ref = np.concatenate([x * c - f32(y * s), x * s + f32(y * c)], axis=-1)
+    bits = inputs.f32_to_bf16_bits(ref.astype(np.float32))
+    differ = np.count_nonzero(host_bits(got["k"]) != bits)
+    say(f"  {differ} of {bits.size} differ")
+    assert differ == 0
