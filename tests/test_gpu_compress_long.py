@@ -1,8 +1,9 @@
 """GPU parity of the compressor's streaming kernel (local blocks past 16384
 rows) against the oracle, bit for bit: the edges of its range and of its
-blocks, and scores that its sampled bracket of the threshold does not fit
-(it misses, or more keys fall inside than are kept), ties and non-numbers at
-the threshold, and shares of more rows than one list holds."""
+blocks, scores that its sampled bracket of the threshold does not fit (it
+misses, or more keys fall inside than are kept), brackets with tied groups at
+their ends or scores that differ in their last bits alone, ties and non-numbers
+at the threshold, and shares of more rows than one list holds."""
 import numpy as np
 import pytest
 
@@ -13,10 +14,33 @@ from gpu_util import host_bits, need_gpu, run_compress, say, upload
 pytestmark = pytest.mark.gpu
 
 
+def _sample(n):
+    """The places whose scores the kernel samples."""
+    i, part = np.arange(4096, dtype=np.uint64), np.uint64(n // 4096)
+    at = (i * np.uint64(0x9e3779b9) % np.uint64(1 << 32)) * part >> np.uint64(32)
+    return i * part + i * np.uint64(n % 4096) // np.uint64(4096) + at
+
+
 def _unsampled(n, rng):
-    """High scores everywhere but at the evenly spaced sample positions."""
+    """High scores everywhere but at the sampled places."""
     s = rng.standard_normal(n).astype(np.float32) + 50
-    s[np.arange(4096) * n // 4096] -= 100
+    s[_sample(n)] -= 100
+    return s
+
+
+def _between_ties(n, rng):
+    """20000 ones, 1000 scores below them, zeros."""
+    s = np.zeros(n, np.float32)
+    s[:20000] = 1
+    s[20000:21000] = rng.uniform(0.1, 0.9, 1000)
+    return rng.permutation(s)
+
+
+def _one_waves_blocks(n, rng):
+    """Scores around the threshold in every 16th block of 256 alone."""
+    s = rng.choice(np.array([-1, 2], np.float32), n)
+    at = np.arange(n) // 256 % 16 == 3
+    s[at] = rng.uniform(0, 1, np.count_nonzero(at))
     return s
 
 
@@ -39,6 +63,15 @@ CASES = {
     "ties_over_capacity": (65536, 26000, 2,
                            lambda n, r: _few_values(n, r, [0, 1, 2], [.1, .5, .4])),
     "bracket_misses": (50000, 25000, 2, _unsampled),
+    "close_scores": (65536, 8192, 2, lambda n, r: 1 + 1e-5 * r.standard_normal(n)),
+    "close_scores_half": (32768, 16384, 2, lambda n, r: 1 + 1e-5 * r.standard_normal(n)),
+    "closer_scores": (30001, 5000, 2, lambda n, r: -3 - 1e-6 * r.standard_normal(n)),
+    "tie_above": (65536, 19990, 1, _between_ties),
+    "between_ties": (65536, 20500, 1, _between_ties),
+    "tie_below": (65536, 21010, 1, _between_ties),
+    "one_waves_blocks": (65536, 32000, 2, _one_waves_blocks),
+    "more_than_kept": (400003, 200000, 1, lambda n, r: r.standard_normal(n)),
+    "few_rows": (20000, 64, 8, lambda n, r: r.standard_normal(n)),
     "zeros_at_threshold": (20000, 10000, 2,
                            lambda n, r: _few_values(n, r, [-1, -0.0, 0.0, 1], [.3, .3, .2, .2])),
     "just_below_zero": (20000, 6000, 2,
