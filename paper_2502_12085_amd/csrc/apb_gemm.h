@@ -400,7 +400,10 @@ gemm_kernel(GemmParams p) {
     ++kk;
     st = st + 1 == NST ? 0 : st + 1;
   };
-  for (; kk + (SPLIT ? 1 : NST) < nk; advance()) step(kk, st, yes, yes);
+  while (kk + (SPLIT ? 1 : NST) < nk) {
+    step(kk, st, yes, yes);
+    advance();
+  }
   if (kk + 1 < nk) {
     step(kk, st, yes, no);
     advance();
@@ -412,7 +415,7 @@ gemm_kernel(GemmParams p) {
   // consecutive features (one 8-byte store).
   if constexpr (EPI == kEpiScorer) {
     // bias, SiLU and this workgroup's share of the second layer: for each of
-    // its 256 tokens and each KV head, the sum over its 256 features of
+    // its tokens and each KV head, the sum over its 256 features of
     // SiLU(acc + b1) * w2, one fp32 partial per feature block
     __syncthreads();  // every wave is done with the LDS stages
     float* const w2_lds = reinterpret_cast<float*>(&a_lds[0][0]);  // [kBF][kScorerMaxKv]
