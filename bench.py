@@ -747,7 +747,7 @@ def main():
         "unmasked_flops": flops,
         "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
-                     "traffic": traffic, "kernel": "attn_fwd_kernel<128>",
+                     "traffic": traffic, "kernel": "attn_fwd_kernel<128, false>",
                      "kernel_source_hash": kernel_source_hash()},
         "paper_context": {"a800_attention_ms_per_block": 34.07,
                           "a800_implied_tflops": round(flops / 34.07e-3 / 1e12, 1),

@@ -160,8 +160,8 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-# What a call costs the host counts: a small decoding step's kernels take 9 us
-# and its launches 5.  The current stream's handle comes from the raw lookup
+# What a call costs the host counts: a small decoding step's kernel takes about
+# 6 us.  The current stream's handle comes from the raw lookup
 # (0.5 us with the device's index; a torch.cuda.Stream object took 3), and a
 # tensor's checks are one expression: 11.7 -> 9.4 us per decode_attention call,
 # 7.9 -> 5.6 per merge_partials call.

@@ -394,7 +394,8 @@ attn_fwd_kernel(Params p) {
       }
     }
   };
-  // Every wave has at most one tile's copies in flight when it waits.
+  // Every wave has at most one tile's copies in flight when it waits.  (SPLIT:
+  // those of two steps; it waits by count.)
   auto land = []() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
 
   const int w_first = r0 + kRowsPerWave * (SPLIT ? wig : wave);

@@ -63,6 +63,7 @@
 #include <type_traits>
 
 #include "apb_internal.h"
+#include "apb_plan.h"
 
 namespace apb {
 namespace {
@@ -77,7 +78,6 @@ constexpr int kBF = 256;        // weight rows (output features) per workgroup
 constexpr int kBK = 64;         // K per step
 constexpr int kGemmThreads = 256;
 constexpr int kPieces = 8;      // 1 KiB weight copy pieces per wave per step
-constexpr int kGemmCus = 256;   // workgroups of one round (one per CU)
 
 enum XMode { kXRowMajor = 0, kXHeadMajor = 1, kXQkv = 2 };
 enum WMode { kWPlain = 0, kWGateUp = 1 };
@@ -529,47 +529,6 @@ gemm_kernel(GemmParams p) {
       }
     }
   }
-}
-
-// How the token tiles of one product are cut: `full` tiles of 256 tokens
-// (NB = 8), then tiles of 32 * nb tokens for the rest.  The chip runs one
-// workgroup per CU, so a product takes whole rounds of 256 tiles, and one
-// with fewer or not quite a multiple of them leaves CUs idle: 80 tiles of 256
-// tokens (1256 tokens x 4096 features) take as long as 256.  Smaller tiles
-// cost more per token (a step's copies of the weight slab do not shrink), so
-// the cut is the cheapest by kTiles: the time of one round in units of a
-// 256-token round, measured at K = 4096 to 14336 (O projection of 1256 tokens:
-// 109 us in 80 tiles of 256 tokens, 65 us in 160 of 128, 57 us in 224 of 96,
-// 45 us per round of 64).  A second launch costs its ramp (kSecond).
-struct GemmSplit {
-  int full, nb;
-};
-
-// Rounds of workgroups (one per CU; every XCD gets an eighth of the tiles).
-inline int64_t gemm_rounds(int64_t tiles) { return (tiles + kGemmCus - 1) / kGemmCus; }
-
-inline GemmSplit gemm_split(int64_t T, int64_t nfy) {
-  static const struct { int nb; double cost; } kTiles[] = {{8, 1.0}, {4, 0.54}, {3, 0.50}, {2, 0.43}};
-  constexpr double kSecond = 0.08;
-  const int64_t most = T / 256;  // whole 256-token tiles
-  GemmSplit best{0, 8};
-  double best_cost = (double)gemm_rounds((T + 255) / 256 * nfy);
-  for (const auto& k : kTiles) {
-    if (k.nb == 8) continue;
-    // whole rounds of 256-token tiles first, as many as fit or fewer
-    const int64_t all = gemm_rounds(most * nfy);
-    for (int64_t r = all > 2 ? all - 2 : 0; r <= all; ++r) {
-      const int64_t full = std::min<int64_t>(most, r * kGemmCus / nfy);
-      const int64_t rest = (T - 256 * full + 32 * k.nb - 1) / (32 * k.nb);
-      const double cost = (double)gemm_rounds(full * nfy) + (double)gemm_rounds(rest * nfy) * k.cost +
-                          (full > 0 && rest > 0 ? kSecond : 0.0);
-      if (cost < best_cost) {
-        best_cost = cost;
-        best = GemmSplit{(int)full, k.nb};
-      }
-    }
-  }
-  return best;
 }
 
 template <int XM, int WM, int EPI, int NB, bool EARLY>

@@ -23,7 +23,8 @@ pytestmark = pytest.mark.gpu
     (3, 1, 64, 1, 6145, 1024),      # 128, ragged
     (2, 1, 64, 0, 8192, 1024),      # 128: the last length of one round
     (4, 2, 128, 0, 8193, 1024),     # 256, one token over a tile
-    (1, 1, 64, 7, 17001, 1024),     # one round of 256, then 64
+    (1, 1, 64, 7, 17001, 1024),     # three rounds of 96
+    (1, 1, 64, 7, 18500, 1024),     # one round of 256, then 64, the last of 4 tokens
 ])
 def test_scorer_tile_widths(shape):
     say(f"[tile widths] scorer {shape}")
@@ -54,7 +55,9 @@ def test_layer_tile_widths(rows):
     (64, 200, 1024),     # 64-token tiles, the last of 8 tokens
     (128, 5000, 1024),   # 96
     (64, 8192, 1024),    # 128
-    (64, 17001, 1024),   # 256, then 64
+    (64, 17001, 1024),   # 96 in three rounds
+    (64, 18500, 1024),   # 256, then 64
+    (64, 20500, 1024),   # 256, then 96
     (128, 9000, 256),    # 64 in one feature tile
 ])
 def test_equal_tokens_score_alike(d, lb, hidden):

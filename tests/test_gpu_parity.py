@@ -322,7 +322,7 @@ def test_compress_edge_cases(case):
                                   "lp_near_lb", "lp_one"])
 def test_compress_long_local_blocks(case):
     """Local blocks past 65536 rows (the paper's 1024K prefill setting over 8
-    hosts has l_b = 131072): the multi-pass selection kernel, bit-exact."""
+    hosts has l_b = 131072): the streaming selection kernel, bit-exact."""
     need_gpu()
     rng = np.random.default_rng(zlib.crc32(case.encode()))
     n_kv, la, d = 2, 16, 128

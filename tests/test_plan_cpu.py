@@ -8,6 +8,7 @@ import pytest
 
 import test_gpu_attention_split as attention_forms
 import test_gpu_decode_groups as decode_forms
+import test_zz_no_alloc as no_alloc
 from paper_2502_12085_amd import apb
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
@@ -28,6 +29,10 @@ int main() {
       const apb::DecodePlan p = apb::plan_decode(a[0], a[1], (int)a[2], a[3], a[4], a[5] != 0, a[6]);
       printf("%d %d %d %d %d %llu\n", p.waves, p.one_launch, p.n_split, p.blocks_per_split,
              p.row_blocks, (unsigned long long)p.workspace_bytes);
+    } else if (!strcmp(rule, "gemm")) {
+      if (scanf("%lld %lld", &a[0], &a[1]) != 2) return 1;
+      const apb::GemmSplit p = apb::gemm_split(a[0], a[1]);
+      printf("%d %d\n", p.full, p.nb);
     } else {
       return 1;
     }
@@ -123,6 +128,8 @@ def test_decode_forms_of_the_gpu_tests(plan):
     for s, _ in decode_forms.SHORT:
         assert _decode(plan, *s)[0] == 1, s
     assert _decode(plan, 8, 2, 128, 36000, 25, 0)[0] == 4  # its NaN test
+    assert [_decode(plan, *s[:6], apb.NOALLOC_SCRATCH_BYTES)[0] for s in no_alloc.CALLS] == \
+        [8, 8, 4, "one launch", 1]
 
 
 @pytest.mark.parametrize("shape, form", [
@@ -159,3 +166,34 @@ def test_decode_plan_within_a_limit(plan):
     assert _decode(plan, 8, 2, 128, 300, 1, 1, part) == (1, 1, 10)
     assert _decode(plan, 8, 2, 128, 300, 1, 1, 2 * part) == ("one launch", 1, 10)
     assert _decode(plan, 8, 2, 128, 8000, 1, 1, 3 * part) == (1, 3, 84)
+
+
+@pytest.mark.parametrize("tokens, features, cut", [
+    # tokens, 256-feature tiles; 256-token tiles and the width of the others.  The
+    # scorer's shapes of the GPU tests:
+    (1, 4, (0, 64)),
+    (65, 4, (0, 64)),
+    (4096, 4, (0, 64)),
+    (4097, 4, (0, 96)),
+    (6144, 4, (0, 96)),
+    (6145, 4, (0, 128)),
+    (8192, 4, (0, 128)),
+    (8193, 4, (33, 256)),
+    (17001, 4, (0, 96)),
+    (18500, 4, (64, 64)),
+    (20500, 4, (64, 96)),
+    (200, 4, (0, 64)),
+    (5000, 4, (0, 96)),
+    (9000, 1, (0, 64)),
+    # the layer's
+    (600, 32, (0, 96)),
+    (1000, 32, (0, 128)),
+    # whole rounds
+    (16384, 4, (64, 256)),
+    (2048, 32, (8, 256)),
+])
+def test_gemm_cut(plan, tokens, features, cut):
+    full, nb = plan("gemm", tokens, features)
+    got = (full, 32 * nb) if nb < 8 else (-(-tokens // 256), 256)
+    assert got == cut
+    assert nb == 8 or 256 * full <= tokens

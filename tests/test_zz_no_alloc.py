@@ -21,10 +21,14 @@ pytestmark = pytest.mark.gpu
 # n_q, n_kv, d, Lc, n_new, append, capped: the first problem's default plan
 # needs 8 splits of 8192 rows (eight-wave path, fp16 partials: 17.3 MB > the
 # 16 MiB scratch) and runs with 7; the second is the 128K Llama-8B-shaped
-# question step (14.1 MB, fits); the third a small one-wave problem.
+# question step (14.1 MB, fits); the third shares each key block among four
+# waves (85 rows); the fourth is one launch, which leaves the scratch alone; the
+# last a small one-wave problem.
 CALLS = [
     (64, 8, 128, 16384, 128, 1, True),
     (32, 8, 128, 16384, 64, 1, False),
+    (40, 8, 128, 9300, 17, 1, False),
+    (32, 8, 128, 300, 4, 1, False),
     (8, 2, 64, 1000, 3, 1, False),
 ]
 
