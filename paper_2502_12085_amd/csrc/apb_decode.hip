@@ -140,9 +140,9 @@ constexpr int kPingPongKB = kTileBlocks;
 // wave w of a group owns the 32-row block w, and a group's waves share its
 // copies, two copying K and two V (a wave without rows only copies).  One barrier
 // per block orders copies and reads; the groups' results meet in LDS, so that a
-// split is one partial.  W = 1 with KS groups is the one-launch form: one split,
-// whose partial is the result.
-template <int D, int W, int KS, int RING>
+// split is one partial.  W = 1 with KS groups is the one-launch form.  WHOLE: one
+// split, whose partial is the result.
+template <int D, int W, int KS, int RING, bool WHOLE>
 __global__ void __launch_bounds__(64 * W * KS, (W * KS + 3) / 4) decode_partial_kernel(DecParams p) {
   constexpr int BK = kKeys;                  // keys per ring block
   constexpr int NKC = D / 16;                // MFMA k-steps over head_dim
@@ -453,7 +453,6 @@ __global__ void __launch_bounds__(64 * W * KS, (W * KS + 3) / 4) decode_partial_
   }
   if (!row_ok) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const bool zero = gridDim.x == 1 && !(l_tot > 0.f);  // the result of no part
   float* orow = p.part_o + ((size_t)split * p.rows_total + grow) * D;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -461,7 +460,8 @@ __global__ void __launch_bounds__(64 * W * KS, (W * KS + 3) / 4) decode_partial_
     for (int g = 0; g < 4; ++g) {
       f32x4 w;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = zero ? 0.f : oacc[db][4 * g + i] * inv;
+      for (int i = 0; i < 4; ++i)  // (a result without any part is zero)
+        w[i] = WHOLE && !(l_tot > 0.f) ? 0.f : oacc[db][4 * g + i] * inv;
       *reinterpret_cast<f32x4*>(orow + 32 * db + 8 * g + 4 * h) = w;
     }
   if (h == 0)
@@ -990,21 +990,25 @@ hipError_t decode_scratch(void** ptr) {
   return hipSuccess;
 }
 
-template <int D>
+template <int D, bool WHOLE>
 static void launch_partials(const DecParams& p, const DecodePlan& pl, dim3 grid, hipStream_t stream) {
+  if (pl.waves == 4)
+    hipLaunchKernelGGL((decode_partial_kernel<D, 4, 2, kGroupRing, WHOLE>), grid, dim3(512), 0, stream, p);
+  else
+    hipLaunchKernelGGL((decode_partial_kernel<D, 1, 1, kRing, WHOLE>), grid, dim3(64), 0, stream, p);
+}
+
+template <int D>
+static void launch_splits(const DecParams& p, const DecodePlan& pl, dim3 grid, hipStream_t stream) {
   constexpr int G = one_launch_groups(D);
-  if (pl.one_launch) {
-    hipLaunchKernelGGL((decode_partial_kernel<D, 1, G, 2>), grid, dim3(64 * G), 0, stream, p);
-    return;
-  }
-  switch (pl.waves) {
-    case 8: hipLaunchKernelGGL((decode_pingpong_kernel<D>), grid, dim3(512), 0, stream, p); break;
-    case 4:
-      hipLaunchKernelGGL((decode_partial_kernel<D, 4, 2, kGroupRing>), grid, dim3(512), 0, stream, p);
-      break;
-    default:
-      hipLaunchKernelGGL((decode_partial_kernel<D, 1, 1, kRing>), grid, dim3(64), 0, stream, p);
-  }
+  if (pl.one_launch)
+    hipLaunchKernelGGL((decode_partial_kernel<D, 1, G, 2, true>), grid, dim3(64 * G), 0, stream, p);
+  else if (pl.waves == 8)
+    hipLaunchKernelGGL((decode_pingpong_kernel<D>), grid, dim3(512), 0, stream, p);
+  else if (pl.n_split == 1)
+    launch_partials<D, true>(p, pl, grid, stream);
+  else
+    launch_partials<D, false>(p, pl, grid, stream);
 }
 
 hipError_t launch_decode(const DecodeArgs& a, const DecodePlan& pl, hipStream_t stream) {
@@ -1032,8 +1036,8 @@ hipError_t launch_decode(const DecodeArgs& a, const DecodePlan& pl, hipStream_t 
   p.blocks_per_split = pl.blocks_per_split;
   p.scale_log2 = a.scale_log2;
   const dim3 grid((unsigned)pl.n_split, (unsigned)a.n_kv, (unsigned)pl.row_blocks);
-  if (a.head_dim == 128) launch_partials<128>(p, pl, grid, stream);
-  else launch_partials<64>(p, pl, grid, stream);
+  if (a.head_dim == 128) launch_splits<128>(p, pl, grid, stream);
+  else launch_splits<64>(p, pl, grid, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (pl.waves != 8 && pl.n_split == 1) return hipSuccess;
