@@ -825,7 +825,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
   p.n_q = a.n_q; p.n_kv = a.n_kv; p.group = a.n_q / a.n_kv;
   p.xcd_map = (p.n_kv % kXcds) == 0;
   p.scale_log2 = a.scale_log2;
-  const bool split = attention_key_split(p.M, a.La, a.Lp, a.n_q, a.head_dim);
+  const bool split = attention_key_split(p.M, a.La, a.Lp, a.lp, a.n_q, a.head_dim);
   const int bm = split ? kAttnSplitRows : kBM;
   p.n_qtiles = (p.M + bm - 1) / bm;
   const dim3 grid((unsigned)(p.n_qtiles * p.n_q));

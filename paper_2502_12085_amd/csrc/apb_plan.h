@@ -14,8 +14,8 @@ constexpr int kCus = 256;  // MI355X; the kernels below run one workgroup per CU
 constexpr int kAttnRows = 256;       // query rows per workgroup of the 256-row form
 constexpr int kAttnSplitRows = 128;  // of the key-split form
 
-// Whether attention over M rows (La of them anchor rows), Lp passed keys and n_q
-// heads takes the key-split form.  In the 256-row form a problem of at most one
+// Whether attention over M rows (La of them anchor rows), Lp passed keys in blocks
+// of lp and n_q heads takes the key-split form.  In the 256-row form a problem of at most one
 // round of workgroups takes as long as its longest row block, whose keys it walks
 // alone; past one round the chip is full either way and that form does less work
 // per key (a K or V tile serves twice the rows).  The key-split form takes about
@@ -38,17 +38,26 @@ constexpr int kAttnSplitRows = 128;  // of the key-split form
 //    heads of d = 64, 191 against 202 (144 CUs, 1.71 against 1.58); 4508 and
 //    5944, 14 / 2 heads, 171 against 194 (252 CUs, 1.84 against 1.76).
 // It needs keys for both groups: 100 rows of d = 64, one tile, 8.2 against 9.1.
-inline bool attention_key_split(int64_t M, int64_t La, int64_t Lp, int64_t n_q, int64_t head_dim) {
-  const int64_t total = M + Lp;  // keys of the last row
+// And a tile that holds a passed block whole has its rows looked up one by one,
+// which the 256-row form does half as often per key: such a key counts 0.85 more
+// (many hosts that pass on less than a tile each: 63 blocks of 20 keys before 550
+// rows of 8 / 2 heads of d = 64 47.7 against 53.7 us, 125 of 20 before 1900 rows of
+// 32 / 8 heads of d = 128 120 against 214; 15 of 20 before 550 rows 38.3 -> 30.3).
+inline bool attention_key_split(int64_t M, int64_t La, int64_t Lp, int64_t lp, int64_t n_q,
+                                int64_t head_dim) {
+  const int64_t total = M + Lp, tile = 8192 / head_dim;  // keys of the last row, of a tile
   const int64_t row_wgs = (M + kAttnRows - 1) / kAttnRows * n_q;
-  if (row_wgs > kCus || total <= 8192 / head_dim) return false;
+  if (row_wgs > kCus || total <= tile) return false;
+  // passed keys in such tiles: all up to lp = tile / 2, none from a tile on
+  const int64_t looked = Lp > 0 ? Lp * std::min(std::max<int64_t>(tile - lp, 0), lp) / lp : 0;
+  const int64_t more = looked * 17 / 20;
   const int64_t tiles = (M + kAttnSplitRows - 1) / kAttnSplitRows;
-  if (tiles * n_q <= kCus) return true;
+  if (tiles * n_q <= kCus) return 100 * (total + more) <= (head_dim == 128 ? 160 : 145) * total;
   // the first block of the second round, and the keys of its last row
   const int64_t r = std::min((tiles - kCus / n_q) * kAttnSplitRows, M) - 1;
   const int64_t second = (r < La ? r : r + Lp) + 1, fixed = head_dim == 128 ? 128 : 512;
   const int64_t rate = std::min<int64_t>(461 + row_wgs, head_dim == 128 ? 707 : 676);  // x 384
-  return 384 * (total + second + fixed) <= rate * total;
+  return 384 * (total + second + fixed + 2 * more) <= rate * total;
 }
 
 // How a decode call splits its keys; the workspace holds one partial per

@@ -22,8 +22,8 @@ int main() {
   long long a[8];
   while (scanf("%31s", rule) == 1) {
     if (!strcmp(rule, "attention")) {
-      for (int i = 0; i < 5; ++i) if (scanf("%lld", &a[i]) != 1) return 1;
-      printf("%d\n", (int)apb::attention_key_split(a[0], a[1], a[2], a[3], a[4]));
+      for (int i = 0; i < 6; ++i) if (scanf("%lld", &a[i]) != 1) return 1;
+      printf("%d\n", (int)apb::attention_key_split(a[0], a[1], a[2], a[3], a[4], a[5]));
     } else if (!strcmp(rule, "decode")) {
       for (int i = 0; i < 7; ++i) if (scanf("%lld", &a[i]) != 1) return 1;
       const apb::DecodePlan p = apb::plan_decode(a[0], a[1], (int)a[2], a[3], a[4], a[5] != 0, a[6]);
@@ -58,7 +58,7 @@ def plan(tmp_path_factory):
 
 
 def _key_split(plan, n_hosts, host, la, lb, lp, n_q, n_kv, d):
-    return plan("attention", la + lb, la, host * lp, n_q, d) == [1]
+    return plan("attention", la + lb, la, host * lp, lp, n_q, d) == [1]
 
 
 def test_attention_forms_of_the_gpu_tests(plan):
@@ -95,6 +95,16 @@ def test_attention_forms_of_the_gpu_tests(plan):
     # the second round has anchor blocks alone
     ((8, 7, 1152, 1024, 1024, 32, 8, 64), False),
     ((8, 7, 1024, 1024, 1024, 32, 8, 128), True),
+    # many passed blocks in a tile
+    ((16, 15, 50, 500, 20, 32, 8, 128), True),
+    ((64, 63, 50, 500, 20, 8, 2, 64), False),
+    ((128, 127, 30, 700, 30, 32, 8, 128), False),
+    ((26, 25, 0, 1900, 20, 32, 8, 128), False),
+    ((17, 16, 0, 1900, 60, 32, 8, 128), True),
+    ((26, 25, 0, 1900, 100, 32, 8, 128), True),
+    ((26, 25, 0, 600, 100, 4, 1, 64), True),
+    ((8, 7, 0, 300, 300, 4, 1, 64), True),
+    ((8, 7, 20, 200, 12, 32, 8, 128), True),
     # past one round of 256-row workgroups
     ((1, 0, 0, 2049, 0, 32, 8, 128), False),
     ((1, 0, 0, 1, 0, 257, 257, 128), False),
