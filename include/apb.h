@@ -173,7 +173,8 @@ apb_status_t apb_scorer_workspace_size(const apb_scorer_problem_t* p, uint64_t* 
  *   workspace, workspace_bytes  caller-owned device scratch of at least
  *                   apb_scorer_workspace_size() bytes, 16-byte aligned.
  * Arithmetic: bf16 products with fp32 accumulation for the first layer, fp32
- * bias, SiLU and second layer; deterministic (fixed summation order).
+ * bias, SiLU and second layer; deterministic (fixed summation order, the same
+ * for every token: equal tokens have equal scores, in blocks of any length).
  */
 apb_status_t apb_retaining_scores(const apb_scorer_problem_t* p, const uint16_t* q,
                                   const uint16_t* k, const uint16_t* v, const uint16_t* w1,
