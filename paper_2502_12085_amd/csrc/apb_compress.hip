@@ -51,8 +51,8 @@ constexpr int kRegWaves = kRegThreads / 64;
 constexpr int kSelBins = 2 * kRegThreads;  // 11-bit digits, two bins per thread
 // Longest block of the register kernel: with 16 keys per thread it takes 13.8 us
 // where the streaming one takes 17.5 (16384 N(0,1) scores, 8 KV heads, l_p =
-// Lb / 8); with 32 keys per thread (and 64, half of them in LDS) it took 21.8
-// against 18.9 us at 20000, 26.2 against 23.7 at 32768, 52.4 against 36.0 at
+// Lb / 8); with 32 keys per thread (and 64, half of them in LDS) it took 22.7
+// against 19.6 us at 20000, 27.6 against 23.5 at 32768, 54.6 against 37.3 at
 // 65536.
 constexpr int kRegMaxKeys = 16 * kRegThreads;
 
@@ -211,7 +211,7 @@ topk_gather_reg_kernel(const float* __restrict__ scores, const uint16_t* __restr
 // ---------------------------------------------------------------------------
 // Long local blocks (Lb > kRegMaxKeys): the scores are streamed from L2 instead
 // of held, and the threshold's digits are not counted over all of them.  At
-// 131072 power-law scores (l_p = 16384, 8 heads of d = 128) a call takes 68 us,
+// 131072 power-law scores (l_p = 16384, 8 heads of d = 128) a call takes 73 us,
 // of which the 139 MB it has to move take 27; radix passes over all scores by
 // 256 threads had taken 655.  Bound by the one pass over the scores (its vector
 // instructions: every workgroup of a head repeats it) and then the gather.
